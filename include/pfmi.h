@@ -245,11 +245,13 @@ pf_status pf_field_device(pf_model *m, int32_t field, void **ptr, int64_t *pitch
  * (asynchronous).  With PF_REDUCE_EACH_STEP the reductions of the state at
  * the start of every step are fused into the step kernel and kept in a
  * device history (pf_reduce_history).  With PF_USE_GRAPH the launches are
- * replayed from captured HIP graphs.  A small 2D Allen-Cahn model (order <=
- * 4, ny a multiple of 16 with (ny / 16) * nx <= 1024, one copy of the grid
- * within 128 KiB) stepped without PF_REDUCE_EACH_STEP or kernel timing runs
- * up to 4096 steps per launch in one workgroup's LDS; the fields are bitwise
- * the same.
+ * replayed from captured HIP graphs.  2D Allen-Cahn, Cahn-Hilliard,
+ * Gray-Scott and Model C models of order 2 or 4 whose tile and time block the
+ * caller has not set run up to 24 steps per launch on register tiles where
+ * that is faster (by a rule on model, order, precision, reductions and size;
+ * such launches are not captured: PF_USE_GRAPH makes no difference); the
+ * fields are bitwise the same, the fused reductions agree to their
+ * compensated accuracy.
  */
 pf_status pf_step(pf_model *m, int64_t nsteps);
 
@@ -317,7 +319,9 @@ pf_status pf_stream(pf_model *m, void **hip_stream);
  * Tile shape of the step kernels: chunk = sites marched per work item along
  * the slowest axis (y in 2D, z in 3D), 0 = the library's choice.  Fields
  * do not depend on it (bitwise); fused reductions agree to their compensated
- * accuracy (the partition into partial sums changes).  pf_get_tile reports the current one and
+ * accuracy (the partition into partial sums changes).  A chunk > 0, like
+ * pf_set_time_block, makes pf_step take this tile (Allen-Cahn grids of at most
+ * 128^2 sites without per-step reductions excepted).  pf_get_tile reports the current one and
  * the kernel family in use (0 fused marching, 1 per-site generic).
  */
 pf_status pf_set_tile(pf_model *m, int32_t chunk);
@@ -376,7 +380,8 @@ int32_t pf_get_passes(const pf_model *m);
 
 /*
  * Autotuner: times each candidate (chunk length, time-block factor, 3D tile
- * layout, passes of a 3D Cahn-Hilliard step) on the model's own buffers by re-running steps from the current
+ * layout, passes of a 3D Cahn-Hilliard step; for 2D models without per-step
+ * reductions also the register tiles of pf_step) on the model's own buffers by re-running steps from the current
  * state (whose buffer is never written, so the state is unchanged), keeps the
  * fastest per step and records it in an in-process cache keyed by (kind,
  * ndim, order, precision, per-step reductions, size class) that later models
@@ -389,8 +394,7 @@ pf_status pf_autotune(pf_model *m, int32_t trials);
 
 /*
  * Kernel timing on the model's stream: while enabled, pf_step records a HIP
- * event pair around every step-kernel launch (graph replay and the
- * whole-grid LDS launches of small models are off);
+ * event pair around every step-kernel launch (graph replay is off);
  * pf_timing_read synchronises and returns the summed kernel milliseconds,
  * the number of launches and the number of time steps they advanced since
  * the last enable (any output pointer may be NULL).

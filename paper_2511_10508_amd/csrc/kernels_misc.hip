@@ -285,6 +285,54 @@ __global__ void __launch_bounds__(kFin) k_finalize2(const double2 *part2, int nb
     }
 }
 
+// Both levels for many steps at once: blockIdx.y is the step.  Level 1 combines
+// a contiguous share of the slots per block and writes the final value itself
+// where one block covers them.
+__global__ void __launch_bounds__(kFin) k_finalize_steps1(const double2 *part, int64_t slots, double2 *part2,
+                                                          double2 *out)
+{
+    __shared__ double sh[kFin], sl[kFin];
+    const int64_t per = (slots + gridDim.x - 1) / gridDim.x;
+    const int64_t lo = (int64_t)blockIdx.x * per, hi = min(slots, lo + per);
+    part += (int64_t)blockIdx.y * kNumQ * slots;
+    for (int q = 0; q < kNumQ; ++q) {
+        Acc a{0.0, 0.0};
+        for (int64_t i = lo + threadIdx.x; i < hi; i += kFin) {
+            const double2 p = part[q * slots + i];
+            acc_add(a, p.x);
+            a.lo += p.y;
+        }
+        const Acc r = block_tree(a, sh, sl);
+        if (threadIdx.x == 0) {
+            if (gridDim.x == 1) {
+                const double s = r.hi + r.lo;
+                out[(int64_t)blockIdx.y * kNumQ + q] = make_double2(s, r.lo - (s - r.hi));
+            } else {
+                part2[((int64_t)blockIdx.y * kNumQ + q) * gridDim.x + blockIdx.x] = make_double2(r.hi, r.lo);
+            }
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kFin) k_finalize_steps2(const double2 *part2, int nb, double2 *out)
+{
+    __shared__ double sh[kFin], sl[kFin];
+    for (int q = 0; q < kNumQ; ++q) {
+        const int64_t at = (int64_t)blockIdx.y * kNumQ + q;
+        Acc a{0.0, 0.0};
+        if ((int)threadIdx.x < nb) {
+            const double2 p = part2[at * nb + threadIdx.x];
+            a.hi = p.x;
+            a.lo = p.y;
+        }
+        const Acc r = block_tree(a, sh, sl);
+        if (threadIdx.x == 0) {
+            const double s = r.hi + r.lo;
+            out[at] = make_double2(s, r.lo - (s - r.hi));
+        }
+    }
+}
+
 // SplitMix64 output finaliser (Steele, Lea and Flood, OOPSLA 2014).
 __device__ __forceinline__ uint64_t mix64(uint64_t z)
 {
@@ -412,6 +460,30 @@ hipError_t launch_finalize(const double2 *part, int64_t pstride, int64_t slots, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_finalize2, dim3(1), dim3(kFin), 0, s, part2, nb, out);
+    return hipGetLastError();
+}
+
+// Blocks per step of the first level: 2048 slots each (8 loads a thread) keep a
+// step of a mid-sized grid in one launch.
+static int finalize_steps_blocks(int64_t slots)
+{
+    return (int)std::max<int64_t>(1, std::min<int64_t>(kFin, cdiv(slots, 2048)));
+}
+
+int64_t finalize_steps_scratch(int64_t slots, int64_t steps)
+{
+    const int nb = finalize_steps_blocks(slots);
+    return nb == 1 ? 0 : (int64_t)kNumQ * nb * steps;
+}
+
+hipError_t launch_finalize_steps(const double2 *part, int64_t slots, int64_t steps, double2 *part2, double2 *out,
+                                 hipStream_t s)
+{
+    const int nb = finalize_steps_blocks(slots);
+    hipLaunchKernelGGL(k_finalize_steps1, dim3(nb, (unsigned)steps), dim3(kFin), 0, s, part, slots, part2, out);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || nb == 1) return e;
+    hipLaunchKernelGGL(k_finalize_steps2, dim3(1, (unsigned)steps), dim3(kFin), 0, s, part2, nb, out);
     return hipGetLastError();
 }
 

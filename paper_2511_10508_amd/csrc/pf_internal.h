@@ -143,18 +143,33 @@ constexpr int kTinyLdsBytes = 128 * 1024;
 bool tiny_available(const Launch &L, int64_t nx, int64_t ny, int64_t nz);
 hipError_t launch_tiny(const Launch &L, const void *table, int32_t blocks, hipStream_t s);
 
-// Many steps of one small Allen-Cahn model in one launch: 2D, r <= 2, ny a
-// multiple of 16 with (ny / 16) * nx <= 1024, the grid (one copy) in
-// kTinyLdsBytes of LDS; each thread holds a 16-row segment of one column in
-// registers between two barriers.  On 64 or 128 columns (r <= columns / 64)
-// and 64 or 128 rows one wave holds a band of whole rows instead
-// (x-neighbours by lane rotation, only the bands' edge rows through LDS, one
-// barrier per step).
-// `args` is the
-// model's StepArgs; the launch reads buf[parity] and leaves the state after
-// `steps` steps in buf[parity ^ (steps & 1)].
-bool lds_steps_available(const Launch &L, int64_t nx, int64_t ny, int64_t nz);
-hipError_t launch_lds_steps(const Launch &L, const void *args, int32_t steps, hipStream_t s);
+// Deep-tile family (2D AC, CH, GS, Model C with r <= 2): `steps` time steps per
+// launch on tiles held in registers (pf_deep2d.h).
+constexpr int kDeepWaves = 16;      // most waves per workgroup
+constexpr int kDeepMaxSteps = 24;   // most steps per launch
+struct DeepArgs {
+    int32_t steps;           // time steps of this launch
+    int32_t hx, hy;          // halo columns and rows per side
+    int32_t ow, oh;          // written columns and rows per tile
+    int32_t tilesx;          // tiles along x
+};
+struct DeepPlan {
+    int32_t wide;            // tile shape: 0 the narrow one, 1 the wide one of the kernel
+    int32_t waves;           // waves per workgroup
+    int32_t tiles;           // workgroups
+    int32_t lds;             // bytes of LDS per workgroup
+    double us;               // estimated microseconds per step
+    DeepArgs args;
+    int64_t slots() const { return (int64_t)tiles * waves; }  // reduction partials per step
+};
+// The tile shape, waves and steps per launch (at most `steps`) with the least
+// estimated time per step; false where the family does not cover L.
+bool plan_deep2d(const Launch &L, int64_t nx, int64_t ny, int64_t steps, bool red, DeepPlan *plan);
+// Sites up to which deep tiles are faster than the marching kernels.
+int64_t deep2d_most_sites(const Launch &L, bool red);
+// Reads buf[parity], writes buf[parity ^ 1] after plan.args.steps steps; with red,
+// step s leaves its partials in part[s kNumQ pstride ..] (pstride = plan.slots()).
+hipError_t launch_deep2d(const Launch &L, const void *args, const DeepPlan &plan, bool red, hipStream_t s);
 
 // Generic per-site family (any r <= kMaxR, 1D, 2D and 3D).  CH runs two
 // passes through `scratch`: one field-sized buffer of T (same pitch as the
@@ -185,6 +200,12 @@ int64_t reduce_partial_slots(int64_t nsites);
 constexpr int kFinSlots = 256;
 hipError_t launch_finalize(const double2 *part, int64_t pstride, int64_t slots, double2 *part2,
                            double2 *out, hipStream_t s);
+
+// The same for `steps` steps at once (step s: part[s kNumQ slots + q slots ..] to
+// out[s kNumQ + q]), part2 holding finalize_steps_scratch(slots, steps) pairs.
+int64_t finalize_steps_scratch(int64_t slots, int64_t steps);
+hipError_t launch_finalize_steps(const double2 *part, int64_t slots, int64_t steps, double2 *part2, double2 *out,
+                                 hipStream_t s);
 
 // Counter-based initial conditions.
 struct InitArgs {

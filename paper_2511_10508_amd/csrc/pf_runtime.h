@@ -33,9 +33,12 @@ struct Model {
     // 3D CH: mu in registers (1) or through `scratch` (2); requested (0: the
     // library's choice), in use
     int passes_req = 0, passes = 1;
-    // small Allen-Cahn grids of the fused family: step calls without per-step
-    // reductions or kernel timing run every step in one workgroup's LDS
-    bool lds_steps = false;
+    // the caller chose a tile, time block, layout or pass count (or the
+    // autotuner found the marching kernels faster): no deep tiles
+    bool pinned = false;
+    bool tuned_deep = false;       // the autotuner found deep tiles faster, whatever the size
+    double2 *deep_part = nullptr;  // reduction partials of several deep-tile launches
+    int64_t deep_part_cap = 0;
     int32_t clen = 0, strips = 0, ow = 0, ytiles = 1, chunks = 0, items = 0, blocks = 0,
             threads = 0;
     int64_t fused_slots = 0;

@@ -245,7 +245,6 @@ static bool plan(Model *m)
     Launch L = m->L;
     const pf_desc &d = m->desc;
     m->family = 1;
-    m->lds_steps = false;
     if (d.flags & PF_SPECTRAL) {
         m->family = 2;
         m->tb = 1;
@@ -283,7 +282,6 @@ static bool plan(Model *m)
         return true;
     }
     m->family = 0;
-    m->lds_steps = lds_steps_available(L, d.n[0], d.n[1], d.n[2]);
     m->strips = strips;
     m->ow = ow;
     m->ytiles = ytiles;
@@ -328,6 +326,7 @@ int32_t default_chunk(const pf_desc *d)
 struct TuneChoice {
     int32_t chunk;
     int tb, rpw, passes;
+    bool deep;  // deep tiles beat every marching candidate
 };
 using TuneKey = std::tuple<int, int, int, int, int, int, int, int>;
 static std::mutex g_tune_mu;
@@ -416,6 +415,22 @@ pf_status set_chunk(Model *m, int32_t chunk)
     return st;
 }
 
+// The event pair around the next timed launch.
+static pf_status timing_events(Model *m, hipEvent_t *e0, hipEvent_t *e1)
+{
+    if (m->ev_used + 2 > m->events.size()) {
+        hipEvent_t a, b;
+        PF_HIP(hipEventCreate(&a), "hipEventCreate");
+        PF_HIP(hipEventCreate(&b), "hipEventCreate");
+        m->events.push_back(a);
+        m->events.push_back(b);
+    }
+    *e0 = m->events[m->ev_used];
+    *e1 = m->events[m->ev_used + 1];
+    m->ev_used += 2;
+    return PF_OK;
+}
+
 // Launch `tb` fused steps from parity `par` (writes 1 - par).  red: fuse the
 // reductions of the state at the start of each of those steps; the finalised
 // results go to res[0 .. kNumQ) and, for tb = 2, res[kNumQ .. 2 kNumQ).
@@ -440,16 +455,8 @@ static pf_status launch_step(Model *m, int par, bool red, double2 *res, bool tim
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
-        if (m->ev_used + 2 > m->events.size()) {
-            hipEvent_t a, b;
-            PF_HIP(hipEventCreate(&a), "hipEventCreate");
-            PF_HIP(hipEventCreate(&b), "hipEventCreate");
-            m->events.push_back(a);
-            m->events.push_back(b);
-        }
-        e0 = m->events[m->ev_used];
-        e1 = m->events[m->ev_used + 1];
-        m->ev_used += 2;
+        pf_status st = timing_events(m, &e0, &e1);
+        if (st != PF_OK) return st;
     }
     if (m->family == 0) {
         if (m->passes == 2) {
@@ -556,7 +563,100 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
     return PF_OK;
 }
 
-constexpr int32_t kLdsLaunchSteps = 4096;  // steps per launch of the whole-grid LDS kernel
+// Whether a call of nsteps steps runs on deep tiles, and its plan: up to the size
+// where the marching kernels overtake them (deep2d_most_sites), or where the
+// autotuner measured them faster.  Small Allen-Cahn grids take them even where the caller chose
+// a tile (a launch per step costs ten times as much there), except for
+// per-step reductions, whose partition the tile defines.
+static bool deep_plan(const Model *m, int64_t nsteps, bool red, DeepPlan *plan)
+{
+    const pf_desc &d = m->desc;
+    if (m->family != 0 || d.ndim != 2 || nsteps < 1) return false;
+    const int64_t N = d.n[0] * d.n[1];
+    if (m->pinned && (red || d.kind != PF_AC || N > 128 * 128)) return false;
+    if (!m->tuned_deep && N > deep2d_most_sites(m->L, red)) return false;
+    return plan_deep2d(m->L, d.n[0], d.n[1], nsteps, red, plan);
+}
+
+constexpr int64_t kDeepPartPairs = 1 << 21;  // partials kept before they are finalised (32 MiB)
+
+// Runs nsteps steps on deep tiles, red: the reductions of every step into hist.
+static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, bool red, double2 *hist, bool timed)
+{
+    const int64_t slots = plan.slots(), per_step = kNumQ * slots;
+    // as many launches as the plan's steps per launch need, the steps shared out evenly
+    const int64_t launches = (nsteps + plan.args.steps - 1) / plan.args.steps;
+    int64_t keep = 0;  // steps whose partials are kept before they are finalised
+    double2 *fin = nullptr;
+    if (red) {
+        keep = std::min<int64_t>(nsteps, std::max<int64_t>(plan.args.steps, kDeepPartPairs / per_step));
+        const int64_t need = keep * per_step + finalize_steps_scratch(slots, keep);
+        if (need > m->deep_part_cap) {
+            if (m->deep_part) {
+                PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
+                PF_HIP(hipFree(m->deep_part), "hipFree(partials)");
+                m->deep_part = nullptr;
+                m->deep_part_cap = 0;
+            }
+            PF_HIP(hipMalloc((void **)&m->deep_part, sizeof(double2) * need), "hipMalloc(partials)");
+            m->deep_part_cap = need;
+        }
+        fin = m->deep_part + keep * per_step;
+    }
+    union {
+        StepArgs<double> d64;
+        StepArgs<float> d32;
+    } u;
+    if (m->fp32)
+        u.d32 = m->a32;
+    else
+        u.d64 = m->a64;
+    DeepPlan p = plan;
+    int64_t done = 0, held = 0;
+    for (int64_t i = 0; i < launches; ++i) {
+        const int64_t k = (nsteps - done + launches - i - 1) / (launches - i);
+        if (red && held + k > keep) {
+            const hipError_t e = launch_finalize_steps(m->deep_part, slots, held, fin,
+                                                       hist + kNumQ * (done - held), m->stream);
+            if (e != hipSuccess) return hip_fail(e, "finalize launch");
+            held = 0;
+        }
+        p.args.steps = (int32_t)k;
+        double2 *part = red ? m->deep_part + held * per_step : nullptr;
+        auto set = [&](auto &a) {
+            a.parity = m->parity;
+            if (red) {
+                a.part = part;
+                a.pstride = slots;
+            }
+        };
+        if (m->fp32)
+            set(u.d32);
+        else
+            set(u.d64);
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        if (timed) {
+            pf_status st = timing_events(m, &e0, &e1);
+            if (st != PF_OK) return st;
+            PF_HIP(hipEventRecord(e0, m->stream), "hipEventRecord");
+        }
+        const hipError_t e = launch_deep2d(m->L, &u, p, red, m->stream);
+        if (e != hipSuccess) return hip_fail(e, "deep-tile step launch");
+        if (timed) PF_HIP(hipEventRecord(e1, m->stream), "hipEventRecord");
+        m->launches++;
+        m->timed_steps += timed ? k : 0;
+        m->parity ^= 1;
+        m->steps_done += k;
+        done += k;
+        held += k;
+    }
+    if (red && held) {
+        const hipError_t e = launch_finalize_steps(m->deep_part, slots, held, fin, hist + kNumQ * (done - held),
+                                                   m->stream);
+        if (e != hipSuccess) return hip_fail(e, "finalize launch");
+    }
+    return PF_OK;
+}
 
 pf_status do_steps(Model *m, int64_t nsteps)
 {
@@ -570,22 +670,8 @@ pf_status do_steps(Model *m, int64_t nsteps)
     }
     const bool use_graph = (m->desc.flags & PF_USE_GRAPH) != 0 && !m->timing;
     int64_t done = 0;
-    if (m->lds_steps && !each && !m->timing) {
-        // the whole grid in one workgroup's LDS, up to kLdsLaunchSteps steps per launch
-        while (done < nsteps) {
-            const int32_t k = (int32_t)std::min<int64_t>(nsteps - done, kLdsLaunchSteps);
-            StepArgs<double> a64 = m->a64;
-            StepArgs<float> a32 = m->a32;
-            a64.parity = a32.parity = m->parity;
-            const hipError_t e = launch_lds_steps(m->L, m->fp32 ? (const void *)&a32 : (const void *)&a64, k,
-                                                  m->stream);
-            if (e != hipSuccess) return hip_fail(e, "LDS step kernel launch");
-            m->parity ^= (k & 1);
-            m->steps_done += k;
-            done += k;
-        }
-        return PF_OK;
-    }
+    DeepPlan dp;
+    if (deep_plan(m, nsteps, each, &dp)) return deep_steps(m, dp, nsteps, each, m->hist, m->timing);
     if (use_graph && nsteps >= 2 * kGraphSteps) {
         if (!m->stage) PF_HIP(hipMalloc((void **)&m->stage, sizeof(double2) * kNumQ * kGraphSteps),
                               "hipMalloc(stage)");
@@ -853,6 +939,8 @@ pf_status model_create(const pf_desc *desc, void *stream, void *const *bufs, int
             m->tb = it->second.tb;
             m->rpw_req = it->second.rpw;
             m->passes_req = it->second.passes;
+            m->pinned = !it->second.deep;
+            m->tuned_deep = it->second.deep;
         }
     }
     st = set_chunk(m, chunk);
@@ -882,6 +970,7 @@ void model_release_async(Model *m)
     dev_free(m, m->part2);
     dev_free(m, m->res);
     dev_free(m, m->hist);
+    if (m->deep_part) (void)hipFree(m->deep_part);
     dev_free(m, m->stage);
     dev_free(m, m->scratch);
     spectral_release(m);
@@ -910,6 +999,7 @@ void pf_destroy_model(Model *m)
     if (m->res) (void)hipFree(m->res);
     if (m->part2) (void)hipFree(m->part2);
     if (m->hist) (void)hipFree(m->hist);
+    if (m->deep_part) (void)hipFree(m->deep_part);
     if (m->stage) (void)hipFree(m->stage);
     if (m->scratch) (void)hipFree(m->scratch);
     spectral_release(m);
@@ -1020,7 +1110,7 @@ pf_status autotune(Model *m, int32_t trials)
     double2 *scratch = nullptr;
     if (red) PF_HIP(hipMalloc((void **)&scratch, sizeof(double2) * kNumQ * 2), "hipMalloc(tune)");
     float best = 1e30f;
-    TuneChoice bestc{keep_c, keep_tb, keep_rpw, keep_passes};
+    TuneChoice bestc{keep_c, keep_tb, keep_rpw, keep_passes, false};
     pf_status st = PF_OK;
     // (tb, rpw, passes): every time block and 3D tile layout in one pass, and
     // the two-pass form where it exists
@@ -1058,17 +1148,51 @@ pf_status autotune(Model *m, int32_t trials)
                 ms /= (float)reps * tb;
                 if (st == PF_OK && ms < best) {
                     best = ms;
-                    bestc = {c, tb, m->rpw_req, passes};
+                    bestc = {c, tb, m->rpw_req, passes, false};
                 }
             }
             if (st != PF_OK) break;
         }
         if (st != PF_OK) break;
     }
+    // deep tiles, the same way (not with per-step reductions, which the chosen
+    // tile partitions)
+    m->pinned = false;
+    m->tuned_deep = true;
+    DeepPlan dp;
+    if (st == PF_OK && !red && deep_plan(m, 1 << 20, false, &dp)) {
+        union {
+            StepArgs<double> d64;
+            StepArgs<float> d32;
+        } u;
+        if (m->fp32) {
+            u.d32 = m->a32;
+            u.d32.parity = m->parity;
+        } else {
+            u.d64 = m->a64;
+            u.d64.parity = m->parity;
+        }
+        hipError_t e = launch_deep2d(m->L, &u, dp, false, m->stream);
+        int reps = trials;
+        float ms = 0;
+        for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
+            (void)hipEventRecord(a, m->stream);
+            for (int t = 0; t < reps && e == hipSuccess; ++t) e = launch_deep2d(m->L, &u, dp, false, m->stream);
+            (void)hipEventRecord(b, m->stream);
+            (void)hipEventSynchronize(b);
+            (void)hipEventElapsedTime(&ms, a, b);
+            if (pass > 0 || ms >= kTuneMinMs || !(ms > 0.f)) break;
+            reps = std::min(64, (int)std::ceil(reps * kTuneMinMs / ms));
+        }
+        if (e != hipSuccess) st = hip_fail(e, "deep-tile step launch");
+        bestc.deep = st == PF_OK && ms / ((float)reps * dp.args.steps) < best;
+    }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     if (scratch) (void)hipFree(scratch);
     if (st != PF_OK) return st;
+    m->pinned = !bestc.deep;
+    m->tuned_deep = bestc.deep;
     m->tb = bestc.tb;
     m->rpw_req = bestc.rpw;
     m->passes_req = bestc.passes;
@@ -1373,6 +1497,7 @@ PF_API pf_status pf_set_tile(pf_model *m, int32_t chunk)
 {
     if (!m || chunk < 0) return fail(PF_ERR_ARG, "bad argument");
     PF_HIP(hipStreamSynchronize(M(m)->stream), "hipStreamSynchronize");
+    if (chunk > 0) M(m)->pinned = true;
     return set_chunk(M(m), chunk);
 }
 
@@ -1392,6 +1517,7 @@ PF_API pf_status pf_set_time_block(pf_model *m, int32_t tb)
     if (tb == 2 && (!time_block_available(mm->L) || mm->desc.flags & PF_FORCE_GENERIC))
         return fail(PF_ERR_UNSUPPORTED, "two-step kernels exist for 2D orders 2 and 4 and 3D order 2");
     mm->tb = tb;
+    mm->pinned = true;
     pf_status st = set_chunk(mm, mm->clen);
     if (st == PF_OK && mm->tb != tb) return fail(PF_ERR_UNSUPPORTED, "two-step kernel not available");
     return st;
