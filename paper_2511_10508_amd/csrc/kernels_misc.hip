@@ -389,6 +389,20 @@ __global__ void __launch_bounds__(256) k_init(InitArgs a)
     }
 }
 
+template <typename T>
+__global__ void __launch_bounds__(256) k_window(WindowArgs a)
+{
+    const T *f = static_cast<const T *>(a.f);
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.count; i += (int64_t)gridDim.x * 256) {
+        const int64_t s = a.first + i, row = s / a.w[0];
+        int64_t x = a.o[0] + (s - row * a.w[0]), y = a.o[1] + row % a.w[1], z = a.o[2] + row / a.w[1];
+        if (x >= a.n[0]) x -= a.n[0];  // origins and extents are below n
+        if (y >= a.n[1]) y -= a.n[1];
+        if (z >= a.n[2]) z -= a.n[2];
+        a.out[i] = (double)f[z * a.plane + y * a.pitch + x];
+    }
+}
+
 __global__ void __launch_bounds__(256) k_copy(float4 *__restrict__ dst,
                                               const float4 *__restrict__ src, int64_t n)
 {
@@ -492,6 +506,16 @@ hipError_t launch_init(const InitArgs &a, hipStream_t s)
     const int64_t N = a.nx * a.ny * a.nz;
     const int64_t blocks = std::min<int64_t>(cdiv(N, 256), 65536);
     hipLaunchKernelGGL(k_init, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_window(const WindowArgs &a, hipStream_t s)
+{
+    const unsigned blocks = (unsigned)std::min<int64_t>(cdiv(a.count, 256), 2048);
+    if (a.fp32)
+        hipLaunchKernelGGL(k_window<float>, dim3(blocks), dim3(256), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_window<double>, dim3(blocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -222,6 +222,18 @@ struct InitArgs {
 };
 hipError_t launch_init(const InitArgs &a, hipStream_t s);
 
+// Sites [first, first + count) of a box of a field (x fastest), wrapped and
+// widened into out (device-visible host memory).
+struct WindowArgs {
+    const void *f;
+    double *out;
+    int32_t fp32;
+    int64_t pitch, plane;
+    int64_t n[3], o[3], w[3];  // grid, origin (0 <= o < n), extent
+    int64_t first, count;
+};
+hipError_t launch_window(const WindowArgs &a, hipStream_t s);
+
 // Plain streaming copy (16-byte vectors), for bandwidth calibration.
 hipError_t launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);
 

@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "../../include/pfmi.h"
+#include "pf_host_copy.h"
 #include "pf_internal.h"
 
 namespace pf {
@@ -54,6 +55,8 @@ struct Model {
     double2 *stage = nullptr;    // graph staging rows [kGraphSteps][kNumQ]
     void *scratch = nullptr;     // CH mu buffer(s) of the per-site family or of a two-pass plan
     void *spec = nullptr;        // spectral scheme state (family 2): plans and half spectra
+
+    PinnedStage pin;             // halves of host transfers
 
     struct Graph {
         hipGraph_t graph = nullptr;

@@ -971,6 +971,7 @@ void model_release_async(Model *m)
     dev_free(m, m->res);
     dev_free(m, m->hist);
     if (m->deep_part) (void)hipFree(m->deep_part);
+    m->pin.release();
     dev_free(m, m->stage);
     dev_free(m, m->scratch);
     spectral_release(m);
@@ -1000,6 +1001,7 @@ void pf_destroy_model(Model *m)
     if (m->part2) (void)hipFree(m->part2);
     if (m->hist) (void)hipFree(m->hist);
     if (m->deep_part) (void)hipFree(m->deep_part);
+    m->pin.release();
     if (m->stage) (void)hipFree(m->stage);
     if (m->scratch) (void)hipFree(m->scratch);
     spectral_release(m);
@@ -1344,20 +1346,9 @@ PF_API pf_status pf_set_field(pf_model *mm, int32_t field, const double *host, i
     const pf_desc &d = m->desc;
     const int64_t N = d.n[0] * d.n[1] * d.n[2];
     if (count != N) return fail(PF_ERR_ARG, "count must equal the number of sites");
-    const size_t ts = tsize(m);
-    std::vector<unsigned char> stage;
-    const void *src = host;
-    if (m->fp32) {
-        stage.resize(ts * (size_t)N);
-        float *s = reinterpret_cast<float *>(stage.data());
-        for (int64_t i = 0; i < N; ++i) s[i] = (float)host[i];
-        src = s;
-    }
     spectral_invalidate(m);
-    PF_HIP(hipMemcpy2DAsync(m->buf[field][m->parity], ts * m->pitch, src, ts * d.n[0], ts * d.n[0],
-                            d.n[1] * d.n[2], hipMemcpyHostToDevice, m->stream),
-           "hipMemcpy2DAsync(set_field)");
-    PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
+    PF_HIP(copy_field_in(m->pin, m->buf[field][m->parity], tsize(m), d.n[0], d.n[1] * d.n[2], m->pitch, host, m->stream),
+           "copy(set_field)");
     return PF_OK;
 }
 
@@ -1369,20 +1360,8 @@ PF_API pf_status pf_get_field(pf_model *mm, int32_t field, double *host, int64_t
     const pf_desc &d = m->desc;
     const int64_t N = d.n[0] * d.n[1] * d.n[2];
     if (count != N) return fail(PF_ERR_ARG, "count must equal the number of sites");
-    const size_t ts = tsize(m);
-    if (m->fp32) {
-        std::vector<float> stage((size_t)N);
-        PF_HIP(hipMemcpy2DAsync(stage.data(), ts * d.n[0], m->buf[field][m->parity], ts * m->pitch,
-                                ts * d.n[0], d.n[1] * d.n[2], hipMemcpyDeviceToHost, m->stream),
-               "hipMemcpy2DAsync(get_field)");
-        PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
-        for (int64_t i = 0; i < N; ++i) host[i] = (double)stage[i];
-    } else {
-        PF_HIP(hipMemcpy2DAsync(host, ts * d.n[0], m->buf[field][m->parity], ts * m->pitch,
-                                ts * d.n[0], d.n[1] * d.n[2], hipMemcpyDeviceToHost, m->stream),
-               "hipMemcpy2DAsync(get_field)");
-        PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
-    }
+    PF_HIP(copy_field_out(m->pin, m->buf[field][m->parity], tsize(m), d.n[0], d.n[1] * d.n[2], m->pitch, host, m->stream),
+           "copy(get_field)");
     return PF_OK;
 }
 
@@ -1395,24 +1374,33 @@ PF_API pf_status pf_get_window(pf_model *mm, int32_t field, const int64_t *origi
     const pf_desc &d = m->desc;
     for (int a = 0; a < 3; ++a)
         if (w[a] < 1 || w[a] > d.n[a]) return fail(PF_ERR_ARG, "window extent must be 1..n");
-    const size_t ts = tsize(m);
-    std::vector<unsigned char> row(ts * (size_t)d.n[0]);
-    PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
-    int64_t k = 0;
-    for (int64_t z = 0; z < w[2]; ++z)
-        for (int64_t y = 0; y < w[1]; ++y) {
-            const int64_t zz = ((origin[2] + z) % d.n[2] + d.n[2]) % d.n[2];
-            const int64_t yy = ((origin[1] + y) % d.n[1] + d.n[1]) % d.n[1];
-            const unsigned char *src = static_cast<const unsigned char *>(m->buf[field][m->parity]) +
-                                       ts * (size_t)(zz * m->pitch * d.n[1] + yy * m->pitch);
-            PF_HIP(hipMemcpy(row.data(), src, ts * (size_t)d.n[0], hipMemcpyDeviceToHost),
-                   "hipMemcpy(window row)");
-            for (int64_t x = 0; x < w[0]; ++x) {
-                const int64_t xx = ((origin[0] + x) % d.n[0] + d.n[0]) % d.n[0];
-                host[k++] = m->fp32 ? (double)reinterpret_cast<const float *>(row.data())[xx]
-                                    : reinterpret_cast<const double *>(row.data())[xx];
-            }
-        }
+    // the window's sites gathered, wrapped and widened by a kernel into the pinned
+    // halves, then to the caller
+    const int64_t total = w[0] * w[1] * w[2];
+    PF_HIP(m->pin.ensure((size_t)total * sizeof(double)), "hipHostMalloc(window)");
+    const int64_t step = (int64_t)(m->pin.bytes / sizeof(double));
+    WindowArgs a;
+    a.f = m->buf[field][m->parity];
+    a.fp32 = m->fp32;
+    a.pitch = m->pitch;
+    a.plane = m->pitch * d.n[1];
+    for (int k = 0; k < 3; ++k) {
+        a.n[k] = d.n[k];
+        a.o[k] = ((origin[k] % d.n[k]) + d.n[k]) % d.n[k];
+        a.w[k] = w[k];
+    }
+    hipError_t e = hipSuccess;
+    for (int64_t at = 0; at < total && e == hipSuccess; at += step) {
+        const int64_t n = std::min(step, total - at);
+        a.first = at;
+        a.count = n;
+        a.out = static_cast<double *>(m->pin.half[0]);
+        e = launch_window(a, m->stream);
+        const hipError_t se = hipStreamSynchronize(m->stream);
+        if (e == hipSuccess) e = se;
+        if (e == hipSuccess) std::memcpy(host + at, a.out, (size_t)n * sizeof(double));
+    }
+    if (e != hipSuccess) return hip_fail(e, "window");
     return PF_OK;
 }
 

@@ -122,6 +122,9 @@ struct Server {
     double2 *pinned_pool = nullptr;  // max_slots x kNumQ result pairs (host-pinned)
     std::vector<int> free_slots;
 
+    std::mutex fetch_mu;    // one fetch at a time through the pinned halves
+    PinnedStage fetch_pin;
+
     std::map<ClassKey, int> class_index;
     std::vector<ClassTables> classes;
     std::map<std::vector<int64_t>, hipGraphExec_t> graphs;  // (class, set, steps, grid) -> graph
@@ -794,15 +797,10 @@ PF_API pf_status pf_server_fetch(pf_server *ss, uint64_t ticket, int32_t field, 
     const pf_desc &d = m->desc;
     const int64_t N = d.n[0] * d.n[1] * d.n[2];
     if (count != N) return fail(PF_ERR_ARG, "count must equal the number of sites");
-    const size_t ts = m->fp32 ? 4 : 8;
-    std::vector<unsigned char> stage(ts * (size_t)N);
-    hipError_t e = hipMemcpy2DAsync(stage.data(), ts * d.n[0], m->buf[field][m->parity], ts * m->pitch,
-                                    ts * d.n[0], d.n[1] * d.n[2], hipMemcpyDeviceToHost, s->copy_stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->copy_stream);
+    std::lock_guard<std::mutex> fl(s->fetch_mu);
+    const hipError_t e = copy_field_out(s->fetch_pin, m->buf[field][m->parity], m->fp32 ? 4 : 8, d.n[0], d.n[1] * d.n[2],
+                                        m->pitch, host, s->copy_stream);
     if (e != hipSuccess) return hip_fail(e, "fetch");
-    for (int64_t i = 0; i < N; ++i)
-        host[i] = m->fp32 ? (double)reinterpret_cast<float *>(stage.data())[i]
-                          : reinterpret_cast<double *>(stage.data())[i];
     return PF_OK;
 }
 
@@ -905,6 +903,7 @@ PF_API void pf_server_destroy(pf_server *ss)
         (void)hipEventDestroy(t.join);
     }
     (void)hipHostFree(s->pinned_pool);
+    s->fetch_pin.release();
     (void)hipEventDestroy(s->fork);
     (void)hipEventDestroy(s->tev[0]);
     (void)hipEventDestroy(s->tev[1]);
