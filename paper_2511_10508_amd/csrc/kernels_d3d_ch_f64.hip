@@ -1,0 +1,10 @@
+// 3D deep-tile kernels, FP64 storage: one (precision, kind) pair of the
+// launcher in pf_deep3d_launch.h, instantiated in a file of its own.
+#include "pf_deep3d_launch.h"
+
+namespace pf {
+
+template hipError_t launch_deep3d_kind<double, kCH>(const Launch &, const StepArgs<double> &, const DeepPlan &, bool,
+                                                 hipStream_t);
+
+}  // namespace pf

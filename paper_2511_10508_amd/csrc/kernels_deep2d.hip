@@ -88,6 +88,7 @@ bool plan_deep2d(const Launch &L, int64_t nx, int64_t ny, int64_t steps, bool re
                                 plan->tiles = (int32_t)tiles;
                                 plan->lds = lds;
                                 plan->us = us;
+                                plan->steps = S;
                                 plan->args = DeepArgs{S, hx, hy, (int32_t)(cdiv(cdiv(nx, tx), W) * W),
                                                       (int32_t)cdiv(ny, ty), (int32_t)tx};
                             }
@@ -115,9 +116,8 @@ bool plan_deep2d(const Launch &L, int64_t nx, int64_t ny, int64_t steps, bool re
 //   r = 1: never (1.2-2.5 times at 20000^2);  r = 2: Allen-Cahn never / 3000^2
 //   (0.97), Cahn-Hilliard 1500^2 (1.4) to 3000^2 (0.74), Gray-Scott and
 //   Model C 6000^2 (1.03-1.1) to 12000^2 (0.8)
-//   reductions, r = 1: Allen-Cahn and Gray-Scott never (1.02-1.26) / 3000^2
-//   (1.3-1.6) to 6000^2 (0.8), Cahn-Hilliard and Model C 6000^2 (0.93-1.0) / as
-//   the others;  r = 2: 1500^2 (1.5-3.0) to 3000^2 (0.8-1.3)
+//   reductions, r = 1: Gray-Scott FP64 never (1.26), the others at 3000^2 (0.9-1.2;
+//   1500^2 2.0-2.9);  r = 2: 1500^2 (1.0-2.0) to 3000^2 (0.8-1.0)
 int64_t deep2d_most_sites(const Launch &L, bool red)
 {
     constexpr int64_t M = 1000000, all = INT64_MAX;
@@ -127,18 +127,21 @@ int64_t deep2d_most_sites(const Launch &L, bool red)
         if (L.kind == kAC) return L.fp32 ? 6 * M : all;
         return two ? 36 * M : 3 * M;
     }
-    if (L.r == 1) return L.fp32 ? 12 * M : (L.kind == kAC || L.kind == kGS) ? all : 25 * M;
-    return two && !L.fp32 ? 5 * M / 2 : 4 * M;
+    if (L.r == 1) return L.fp32 ? 7 * M : L.kind == kGS ? all : 9 * M;
+    return two && !L.fp32 ? 2 * M : 7 * M / 2;
 }
 
-hipError_t launch_deep2d(const Launch &L, const void *args, const DeepPlan &plan, bool red, hipStream_t s)
+hipError_t launch_deep2d(const Launch &L, const void *args, const DeepPlan &plan, int32_t steps, bool red,
+                         hipStream_t s)
 {
     hipError_t err = hipErrorInvalidValue;
-    if (plan.args.steps < 1 || plan.args.steps > kDeepMaxSteps || plan.tiles < 1) return err;
+    if (steps < 1 || steps > plan.steps || plan.tiles < 1) return err;
+    DeepPlan p = plan;
+    p.args.steps = steps;
     dispatch_prec(L.fp32, [&](auto tz) {
         using T = decltype(tz);
         dispatch_kind(L.kind, [&](auto kc) {
-            err = launch_deep2d_kind<T, decltype(kc)::value>(L, *static_cast<const StepArgs<T> *>(args), plan, red, s);
+            err = launch_deep2d_kind<T, decltype(kc)::value>(L, *static_cast<const StepArgs<T> *>(args), p, red, s);
         });
     });
     return err;

@@ -248,13 +248,19 @@ __device__ __forceinline__ Acc block_tree(Acc a, double *sh, double *sl)
     return r;
 }
 
-__global__ void __launch_bounds__(kFin) k_finalize1(const double2 *part, int64_t pstride,
-                                                    int64_t slots, double2 *part2)
+// Two fixed-order levels for the partials of many steps at once (blockIdx.y is
+// the step): quantity q of step k has its `slots` pairs at part[(k / tb) kNumQ
+// pstride + q pstride + (k % tb) slots].  Level 1 combines a contiguous share of
+// the slots per block; one block writes the result itself.
+__global__ void __launch_bounds__(kFin) k_finalize1(const double2 *part, int64_t pstride, int64_t slots, int tb,
+                                                    double2 *part2, double2 *out)
 {
     __shared__ double sh[kFin], sl[kFin];
     const int64_t per = (slots + gridDim.x - 1) / gridDim.x;
     const int64_t lo = (int64_t)blockIdx.x * per;
     const int64_t hi = min(slots, lo + per);
+    const int step = blockIdx.y;
+    part += (int64_t)(step / tb) * kNumQ * pstride + (int64_t)(step % tb) * slots;
     for (int q = 0; q < kNumQ; ++q) {
         Acc a{0.0, 0.0};
         for (int64_t i = lo + threadIdx.x; i < hi; i += kFin) {
@@ -263,58 +269,19 @@ __global__ void __launch_bounds__(kFin) k_finalize1(const double2 *part, int64_t
             a.lo += p.y;
         }
         const Acc r = block_tree(a, sh, sl);
-        if (threadIdx.x == 0) part2[q * kFin + blockIdx.x] = make_double2(r.hi, r.lo);
-    }
-}
-
-__global__ void __launch_bounds__(kFin) k_finalize2(const double2 *part2, int nb, double2 *out)
-{
-    __shared__ double sh[kFin], sl[kFin];
-    for (int q = 0; q < kNumQ; ++q) {
-        Acc a{0.0, 0.0};
-        if ((int)threadIdx.x < nb) {
-            const double2 p = part2[q * kFin + threadIdx.x];
-            a.hi = p.x;
-            a.lo = p.y;
-        }
-        const Acc r = block_tree(a, sh, sl);
         if (threadIdx.x == 0) {
-            const double s = r.hi + r.lo;
-            out[q] = make_double2(s, r.lo - (s - r.hi));
-        }
-    }
-}
-
-// Both levels for many steps at once: blockIdx.y is the step.  Level 1 combines
-// a contiguous share of the slots per block and writes the final value itself
-// where one block covers them.
-__global__ void __launch_bounds__(kFin) k_finalize_steps1(const double2 *part, int64_t slots, double2 *part2,
-                                                          double2 *out)
-{
-    __shared__ double sh[kFin], sl[kFin];
-    const int64_t per = (slots + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = (int64_t)blockIdx.x * per, hi = min(slots, lo + per);
-    part += (int64_t)blockIdx.y * kNumQ * slots;
-    for (int q = 0; q < kNumQ; ++q) {
-        Acc a{0.0, 0.0};
-        for (int64_t i = lo + threadIdx.x; i < hi; i += kFin) {
-            const double2 p = part[q * slots + i];
-            acc_add(a, p.x);
-            a.lo += p.y;
-        }
-        const Acc r = block_tree(a, sh, sl);
-        if (threadIdx.x == 0) {
-            if (gridDim.x == 1) {
-                const double s = r.hi + r.lo;
-                out[(int64_t)blockIdx.y * kNumQ + q] = make_double2(s, r.lo - (s - r.hi));
+            const int64_t at = (int64_t)step * kNumQ + q;
+            if (gridDim.x > 1) {
+                part2[at * gridDim.x + blockIdx.x] = make_double2(r.hi, r.lo);
             } else {
-                part2[((int64_t)blockIdx.y * kNumQ + q) * gridDim.x + blockIdx.x] = make_double2(r.hi, r.lo);
+                const double s = r.hi + r.lo;
+                out[at] = make_double2(s, r.lo - (s - r.hi));
             }
         }
     }
 }
 
-__global__ void __launch_bounds__(kFin) k_finalize_steps2(const double2 *part2, int nb, double2 *out)
+__global__ void __launch_bounds__(kFin) k_finalize2(const double2 *part2, int nb, double2 *out)
 {
     __shared__ double sh[kFin], sl[kFin];
     for (int q = 0; q < kNumQ; ++q) {
@@ -466,39 +433,29 @@ hipError_t launch_reduce_state(const Launch &L, const void *args, hipStream_t s)
     return err;
 }
 
+static int finalize_blocks(int64_t slots)
+{
+    return (int)std::max<int64_t>(1, std::min<int64_t>(kFin, cdiv(slots, kFin)));
+}
+
+int64_t finalize_scratch(int64_t slots, int64_t steps) { return (int64_t)kNumQ * finalize_blocks(slots) * steps; }
+
+hipError_t launch_finalize_steps(const double2 *part, int64_t pstride, int64_t slots, int tb, int64_t steps,
+                                 double2 *part2, double2 *out, hipStream_t s)
+{
+    const int nb = finalize_blocks(slots);
+    if (steps < 1 || steps > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_finalize1, dim3(nb, (unsigned)steps), dim3(kFin), 0, s, part, pstride, slots, tb, part2, out);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || nb == 1) return e;
+    hipLaunchKernelGGL(k_finalize2, dim3(1, (unsigned)steps), dim3(kFin), 0, s, part2, nb, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_finalize(const double2 *part, int64_t pstride, int64_t slots, double2 *part2,
                            double2 *out, hipStream_t s)
 {
-    const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(kFin, cdiv(slots, kFin)));
-    hipLaunchKernelGGL(k_finalize1, dim3(nb), dim3(kFin), 0, s, part, pstride, slots, part2);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finalize2, dim3(1), dim3(kFin), 0, s, part2, nb, out);
-    return hipGetLastError();
-}
-
-// Blocks per step of the first level: 2048 slots each (8 loads a thread) keep a
-// step of a mid-sized grid in one launch.
-static int finalize_steps_blocks(int64_t slots)
-{
-    return (int)std::max<int64_t>(1, std::min<int64_t>(kFin, cdiv(slots, 2048)));
-}
-
-int64_t finalize_steps_scratch(int64_t slots, int64_t steps)
-{
-    const int nb = finalize_steps_blocks(slots);
-    return nb == 1 ? 0 : (int64_t)kNumQ * nb * steps;
-}
-
-hipError_t launch_finalize_steps(const double2 *part, int64_t slots, int64_t steps, double2 *part2, double2 *out,
-                                 hipStream_t s)
-{
-    const int nb = finalize_steps_blocks(slots);
-    hipLaunchKernelGGL(k_finalize_steps1, dim3(nb, (unsigned)steps), dim3(kFin), 0, s, part, slots, part2, out);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || nb == 1) return e;
-    hipLaunchKernelGGL(k_finalize_steps2, dim3(1, (unsigned)steps), dim3(kFin), 0, s, part2, nb, out);
-    return hipGetLastError();
+    return launch_finalize_steps(part, pstride, slots, 1, 1, part2, out, s);
 }
 
 hipError_t launch_init(const InitArgs &a, hipStream_t s)

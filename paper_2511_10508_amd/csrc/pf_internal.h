@@ -143,8 +143,8 @@ constexpr int kTinyLdsBytes = 128 * 1024;
 bool tiny_available(const Launch &L, int64_t nx, int64_t ny, int64_t nz);
 hipError_t launch_tiny(const Launch &L, const void *table, int32_t blocks, hipStream_t s);
 
-// Deep-tile family (2D AC, CH, GS, Model C with r <= 2): `steps` time steps per
-// launch on tiles held in registers (pf_deep2d.h).
+// Deep-tile family (2D and 3D AC, CH, GS, Model C with r <= 2): several time
+// steps per launch on tiles held in registers (pf_deep2d.h, pf_deep3d.h).
 constexpr int kDeepWaves = 16;      // most waves per workgroup
 constexpr int kDeepMaxSteps = 24;   // most steps per launch
 struct DeepArgs {
@@ -153,23 +153,35 @@ struct DeepArgs {
     int32_t ow, oh;          // written columns and rows per tile
     int32_t tilesx;          // tiles along x
 };
+constexpr int kDeep3Waves = 8;      // the same of the 3D bricks (pf_deep3d.h)
+struct Deep3Args {
+    int32_t steps, hx, hy, hz, ow, oh, od, tilesx, tilesy;
+};
 struct DeepPlan {
-    int32_t wide;            // tile shape: 0 the narrow one, 1 the wide one of the kernel
+    int32_t wide;            // tile shape: 0 the narrow (3D: flat), 1 the wide (tall) one of the kernel
     int32_t waves;           // waves per workgroup
     int32_t tiles;           // workgroups
     int32_t lds;             // bytes of LDS per workgroup
     double us;               // estimated microseconds per step
-    DeepArgs args;
+    int32_t steps;           // time steps per launch
+    DeepArgs args;           // 2D
+    Deep3Args args3;         // 3D
     int64_t slots() const { return (int64_t)tiles * waves; }  // reduction partials per step
 };
 // The tile shape, waves and steps per launch (at most `steps`) with the least
 // estimated time per step; false where the family does not cover L.
 bool plan_deep2d(const Launch &L, int64_t nx, int64_t ny, int64_t steps, bool red, DeepPlan *plan);
+bool plan_deep3d(const Launch &L, int64_t nx, int64_t ny, int64_t nz, int64_t steps, bool red, DeepPlan *plan);
 // Sites up to which deep tiles are faster than the marching kernels.
 int64_t deep2d_most_sites(const Launch &L, bool red);
-// Reads buf[parity], writes buf[parity ^ 1] after plan.args.steps steps; with red,
-// step s leaves its partials in part[s kNumQ pstride ..] (pstride = plan.slots()).
-hipError_t launch_deep2d(const Launch &L, const void *args, const DeepPlan &plan, bool red, hipStream_t s);
+int64_t deep3d_most_sites(const Launch &L, bool red);
+// Takes `steps` (at most plan.steps) steps from buf[parity] to buf[parity ^ 1]; with
+// red, step s leaves its partials in part[s kNumQ pstride ..] (pstride =
+// plan.slots()).
+hipError_t launch_deep2d(const Launch &L, const void *args, const DeepPlan &plan, int32_t steps, bool red,
+                         hipStream_t s);
+hipError_t launch_deep3d(const Launch &L, const void *args, const DeepPlan &plan, int32_t steps, bool red,
+                         hipStream_t s);
 
 // Generic per-site family (any r <= kMaxR, 1D, 2D and 3D).  CH runs two
 // passes through `scratch`: one field-sized buffer of T (same pitch as the
@@ -201,11 +213,13 @@ constexpr int kFinSlots = 256;
 hipError_t launch_finalize(const double2 *part, int64_t pstride, int64_t slots, double2 *part2,
                            double2 *out, hipStream_t s);
 
-// The same for `steps` steps at once (step s: part[s kNumQ slots + q slots ..] to
-// out[s kNumQ + q]), part2 holding finalize_steps_scratch(slots, steps) pairs.
-int64_t finalize_steps_scratch(int64_t slots, int64_t steps);
-hipError_t launch_finalize_steps(const double2 *part, int64_t slots, int64_t steps, double2 *part2, double2 *out,
-                                 hipStream_t s);
+// The same for `steps` (at most 65535) steps at once into out[step kNumQ + q]:
+// the pairs of step k at part[(k / tb) kNumQ pstride + q pstride + (k % tb) slots],
+// the layout that launches of tb steps leave; part2 holds
+// finalize_scratch(slots, steps) pairs.
+int64_t finalize_scratch(int64_t slots, int64_t steps);
+hipError_t launch_finalize_steps(const double2 *part, int64_t pstride, int64_t slots, int tb, int64_t steps,
+                                 double2 *part2, double2 *out, hipStream_t s);
 
 // Counter-based initial conditions.
 struct InitArgs {

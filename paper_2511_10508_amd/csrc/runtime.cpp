@@ -434,7 +434,10 @@ static pf_status timing_events(Model *m, hipEvent_t *e0, hipEvent_t *e1)
 // Launch `tb` fused steps from parity `par` (writes 1 - par).  red: fuse the
 // reductions of the state at the start of each of those steps; the finalised
 // results go to res[0 .. kNumQ) and, for tb = 2, res[kNumQ .. 2 kNumQ).
-static pf_status launch_step(Model *m, int par, bool red, double2 *res, bool timed, int tb = 1)
+// With `part` the partials go there instead ([quantity][step][slot]) and are
+// left to the caller to finalise (fused family).
+static pf_status launch_step(Model *m, int par, bool red, double2 *res, bool timed, int tb = 1,
+                             double2 *part = nullptr)
 {
     const pf_desc &d = m->desc;
     union {
@@ -453,6 +456,10 @@ static pf_status launch_step(Model *m, int par, bool red, double2 *res, bool tim
         u.d64.red = red;
         ap = &u.d64;
     }
+    if (part) {
+        (m->fp32 ? u.d32.part : u.d64.part) = part;
+        (m->fp32 ? u.d32.pstride : u.d64.pstride) = tb * m->fused_slots;
+    }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
         pf_status st = timing_events(m, &e0, &e1);
@@ -470,7 +477,7 @@ static pf_status launch_step(Model *m, int par, bool red, double2 *res, bool tim
                                                       m->passes == 2 ? m->scratch : nullptr, m->stream);
         if (e != hipSuccess) return hip_fail(e, "step kernel launch");
         if (timed) PF_HIP(hipEventRecord(e1, m->stream), "hipEventRecord");
-        if (red) {
+        if (red && !part) {
             for (int s = 0; s < tb; ++s) {
                 hipError_t f = launch_finalize(m->part + (int64_t)s * m->fused_slots, m->pstride, m->fused_slots,
                                                m->part2, res + kNumQ * s, m->stream);
@@ -533,6 +540,64 @@ static void destroy_graphs(Model *m)
     m->graphs_valid = false;
 }
 
+constexpr int64_t kDeepPartPairs = 1 << 21;  // partials kept before they are finalised (32 MiB)
+
+// Partials of the steps since the last finalising launch, which takes as many
+// steps at once as 32 MiB hold (two launches of 9 us a step otherwise: as long as
+// a step of a 1024^2 grid).
+struct RedBatch {
+    Model *m = nullptr;
+    int64_t slots = 0, keep = 0, held = 0;
+    int tb = 1;              // steps per launch in the partials' layout
+    double2 *out = nullptr;  // results of the first step held
+
+    // room for `unit` steps per launch at least, in whole launches, and for 1024
+    // steps (as the history has), so that a later, longer call finds it in place
+    pf_status begin(Model *model, int64_t slots_, int tb_, int64_t unit, int64_t nsteps, double2 *out_)
+    {
+        m = model;
+        slots = slots_;
+        tb = tb_;
+        out = out_;
+        const int64_t per_step = kNumQ * slots;
+        keep = std::max<int64_t>(unit, std::min<int64_t>(std::min<int64_t>(std::max<int64_t>(nsteps, 1024), 4096), kDeepPartPairs / per_step));
+        keep = (keep + tb - 1) / tb * tb;
+        const int64_t need = keep * per_step + finalize_scratch(slots, keep);
+        if (need <= m->deep_part_cap) return PF_OK;
+        if (m->deep_part) {
+            PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
+            PF_HIP(hipFree(m->deep_part), "hipFree(partials)");
+            m->deep_part = nullptr;
+            m->deep_part_cap = 0;
+            m->graphs_valid = false;  // captured launches hold the old address
+        }
+        PF_HIP(hipMalloc((void **)&m->deep_part, sizeof(double2) * need), "hipMalloc(partials)");
+        m->deep_part_cap = need;
+        return PF_OK;
+    }
+    // where the next k steps leave their partials
+    pf_status take(int64_t k, double2 **part)
+    {
+        if (held + k > keep) {
+            pf_status st = flush();
+            if (st != PF_OK) return st;
+        }
+        *part = m->deep_part + held * kNumQ * slots;
+        held += k;
+        return PF_OK;
+    }
+    pf_status flush()
+    {
+        if (!held) return PF_OK;
+        const hipError_t e = launch_finalize_steps(m->deep_part, tb * slots, slots, tb, held,
+                                                   m->deep_part + keep * kNumQ * slots, out, m->stream);
+        if (e != hipSuccess) return hip_fail(e, "finalize launch");
+        out += kNumQ * held;
+        held = 0;
+        return PF_OK;
+    }
+};
+
 // Capture `k` steps starting at parity `par` (reductions into the staging
 // history rows 0..k-1 when red) as one graph.
 static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph &g)
@@ -540,15 +605,21 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
     g.par = par;
     g.steps = k;
     g.red = red;
+    const bool batch = red && m->family == 0;
+    RedBatch rb;
+    pf_status st = batch ? rb.begin(m, m->fused_slots, m->tb, m->tb, k, m->stage) : PF_OK;
+    if (st != PF_OK) return st;
     PF_HIP(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-    pf_status st = PF_OK;
     int p = par;
     g.launches = 0;
     for (int i = 0; i < k && st == PF_OK; i += m->tb) {
-        st = launch_step(m, p, red, m->stage + kNumQ * i, false, m->tb);
+        double2 *part = nullptr;
+        if (batch) st = rb.take(m->tb, &part);
+        if (st == PF_OK) st = launch_step(m, p, red, m->stage + kNumQ * i, false, m->tb, part);
         p ^= 1;
         g.launches++;
     }
+    if (batch && st == PF_OK) st = rb.flush();
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamEndCapture(m->stream, &graph);
     if (st != PF_OK) {
@@ -571,37 +642,30 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
 static bool deep_plan(const Model *m, int64_t nsteps, bool red, DeepPlan *plan)
 {
     const pf_desc &d = m->desc;
-    if (m->family != 0 || d.ndim != 2 || nsteps < 1) return false;
-    const int64_t N = d.n[0] * d.n[1];
-    if (m->pinned && (red || d.kind != PF_AC || N > 128 * 128)) return false;
-    if (!m->tuned_deep && N > deep2d_most_sites(m->L, red)) return false;
-    return plan_deep2d(m->L, d.n[0], d.n[1], nsteps, red, plan);
+    if (m->family != 0 || d.ndim < 2 || nsteps < 1) return false;
+    const int64_t N = d.n[0] * d.n[1] * d.n[2];
+    if (m->pinned && (red || d.kind != PF_AC || d.ndim != 2 || N > 128 * 128)) return false;
+    if (!m->tuned_deep && N > (d.ndim == 2 ? deep2d_most_sites(m->L, red) : deep3d_most_sites(m->L, red))) return false;
+    return d.ndim == 2 ? plan_deep2d(m->L, d.n[0], d.n[1], nsteps, red, plan)
+                       : plan_deep3d(m->L, d.n[0], d.n[1], d.n[2], nsteps, red, plan);
 }
 
-constexpr int64_t kDeepPartPairs = 1 << 21;  // partials kept before they are finalised (32 MiB)
+static hipError_t launch_deep(const Model *m, const void *args, const DeepPlan &plan, int32_t steps, bool red)
+{
+    return m->desc.ndim == 2 ? launch_deep2d(m->L, args, plan, steps, red, m->stream)
+                             : launch_deep3d(m->L, args, plan, steps, red, m->stream);
+}
 
 // Runs nsteps steps on deep tiles, red: the reductions of every step into hist.
 static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, bool red, double2 *hist, bool timed)
 {
-    const int64_t slots = plan.slots(), per_step = kNumQ * slots;
+    const int64_t slots = plan.slots();
     // as many launches as the plan's steps per launch need, the steps shared out evenly
-    const int64_t launches = (nsteps + plan.args.steps - 1) / plan.args.steps;
-    int64_t keep = 0;  // steps whose partials are kept before they are finalised
-    double2 *fin = nullptr;
+    const int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
+    RedBatch rb;
     if (red) {
-        keep = std::min<int64_t>(nsteps, std::max<int64_t>(plan.args.steps, kDeepPartPairs / per_step));
-        const int64_t need = keep * per_step + finalize_steps_scratch(slots, keep);
-        if (need > m->deep_part_cap) {
-            if (m->deep_part) {
-                PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
-                PF_HIP(hipFree(m->deep_part), "hipFree(partials)");
-                m->deep_part = nullptr;
-                m->deep_part_cap = 0;
-            }
-            PF_HIP(hipMalloc((void **)&m->deep_part, sizeof(double2) * need), "hipMalloc(partials)");
-            m->deep_part_cap = need;
-        }
-        fin = m->deep_part + keep * per_step;
+        pf_status st = rb.begin(m, slots, 1, plan.steps, nsteps, hist);
+        if (st != PF_OK) return st;
     }
     union {
         StepArgs<double> d64;
@@ -611,18 +675,14 @@ static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, bool
         u.d32 = m->a32;
     else
         u.d64 = m->a64;
-    DeepPlan p = plan;
-    int64_t done = 0, held = 0;
+    int64_t done = 0;
     for (int64_t i = 0; i < launches; ++i) {
         const int64_t k = (nsteps - done + launches - i - 1) / (launches - i);
-        if (red && held + k > keep) {
-            const hipError_t e = launch_finalize_steps(m->deep_part, slots, held, fin,
-                                                       hist + kNumQ * (done - held), m->stream);
-            if (e != hipSuccess) return hip_fail(e, "finalize launch");
-            held = 0;
+        double2 *part = nullptr;
+        if (red) {
+            pf_status st = rb.take(k, &part);
+            if (st != PF_OK) return st;
         }
-        p.args.steps = (int32_t)k;
-        double2 *part = red ? m->deep_part + held * per_step : nullptr;
         auto set = [&](auto &a) {
             a.parity = m->parity;
             if (red) {
@@ -640,7 +700,7 @@ static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, bool
             if (st != PF_OK) return st;
             PF_HIP(hipEventRecord(e0, m->stream), "hipEventRecord");
         }
-        const hipError_t e = launch_deep2d(m->L, &u, p, red, m->stream);
+        const hipError_t e = launch_deep(m, &u, plan, (int32_t)k, red);
         if (e != hipSuccess) return hip_fail(e, "deep-tile step launch");
         if (timed) PF_HIP(hipEventRecord(e1, m->stream), "hipEventRecord");
         m->launches++;
@@ -648,14 +708,8 @@ static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, bool
         m->parity ^= 1;
         m->steps_done += k;
         done += k;
-        held += k;
     }
-    if (red && held) {
-        const hipError_t e = launch_finalize_steps(m->deep_part, slots, held, fin, hist + kNumQ * (done - held),
-                                                   m->stream);
-        if (e != hipSuccess) return hip_fail(e, "finalize launch");
-    }
-    return PF_OK;
+    return red ? rb.flush() : PF_OK;
 }
 
 pf_status do_steps(Model *m, int64_t nsteps)
@@ -701,14 +755,31 @@ pf_status do_steps(Model *m, int64_t nsteps)
             m->steps_done += kGraphSteps;
         }
     }
-    while (done < nsteps) {
-        const int tb = (m->tb == 2 && nsteps - done >= 2) ? 2 : 1;
-        pf_status st = launch_step(m, m->parity, each, each ? m->hist + kNumQ * done : nullptr,
-                                   m->timing, tb);
-        if (st != PF_OK) return st;
-        m->parity ^= 1;
-        m->steps_done += tb;
-        done += tb;
+    // launches of m->tb steps, then an odd step by itself; the fused family's
+    // reductions are finalised many steps at a time
+    const bool batch = each && m->family == 0;
+    for (int tb : {m->tb, 1}) {
+        const int64_t n = (nsteps - done) / tb * tb;
+        if (n == 0) continue;
+        RedBatch rb;
+        if (batch) {
+            pf_status st = rb.begin(m, m->fused_slots, tb, tb, n, m->hist + kNumQ * done);
+            if (st != PF_OK) return st;
+        }
+        for (int64_t i = 0; i < n; i += tb) {
+            double2 *part = nullptr;
+            pf_status st = batch ? rb.take(tb, &part) : PF_OK;
+            if (st == PF_OK)
+                st = launch_step(m, m->parity, each, each ? m->hist + kNumQ * done : nullptr, m->timing, tb, part);
+            if (st != PF_OK) return st;
+            m->parity ^= 1;
+            m->steps_done += tb;
+            done += tb;
+        }
+        if (batch) {
+            pf_status st = rb.flush();
+            if (st != PF_OK) return st;
+        }
     }
     return PF_OK;
 }
@@ -1174,12 +1245,12 @@ pf_status autotune(Model *m, int32_t trials)
             u.d64 = m->a64;
             u.d64.parity = m->parity;
         }
-        hipError_t e = launch_deep2d(m->L, &u, dp, false, m->stream);
+        hipError_t e = launch_deep(m, &u, dp, dp.steps, false);
         int reps = trials;
         float ms = 0;
         for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
             (void)hipEventRecord(a, m->stream);
-            for (int t = 0; t < reps && e == hipSuccess; ++t) e = launch_deep2d(m->L, &u, dp, false, m->stream);
+            for (int t = 0; t < reps && e == hipSuccess; ++t) e = launch_deep(m, &u, dp, dp.steps, false);
             (void)hipEventRecord(b, m->stream);
             (void)hipEventSynchronize(b);
             (void)hipEventElapsedTime(&ms, a, b);
@@ -1187,7 +1258,7 @@ pf_status autotune(Model *m, int32_t trials)
             reps = std::min(64, (int)std::ceil(reps * kTuneMinMs / ms));
         }
         if (e != hipSuccess) st = hip_fail(e, "deep-tile step launch");
-        bestc.deep = st == PF_OK && ms / ((float)reps * dp.args.steps) < best;
+        bestc.deep = st == PF_OK && ms / ((float)reps * dp.steps) < best;
     }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
