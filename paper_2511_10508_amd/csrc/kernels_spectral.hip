@@ -1,6 +1,7 @@
 // Element-wise kernels of the semi-implicit Fourier spectral step: the
 // explicit real-space term and the implicit update of the half spectrum.
-// The transforms themselves are hipFFT calls (spectral.cpp).
+// The transforms are hipFFT calls (spectral.cpp), or on power-of-two grids the
+// library's own (pf_fft.h), which do this work themselves.
 #include <algorithm>
 #include <type_traits>
 
@@ -8,6 +9,12 @@
 #include "pf_dispatch.h"
 
 namespace pf {
+
+template <typename T>
+hipError_t launch_fft_rows_t(const StepArgs<T> &a, const FftArgs &f, bool inverse, hipStream_t s);
+template <typename T>
+hipError_t launch_fft_cols_t(const SpecArgs &p, const FftArgs &f, int64_t n, bool along_z, int64_t batches, int mode,
+                             hipStream_t s);
 
 namespace {
 
@@ -80,6 +87,33 @@ dim3 grid_rows(int64_t cols, int64_t rows)
 }
 
 }  // namespace
+
+bool own_fft_available(const Launch &L, int64_t nx, int64_t ny, int64_t nz)
+{
+    auto pow2 = [](int64_t n, int64_t lo, int64_t hi) { return n >= lo && n <= hi && (n & (n - 1)) == 0; };
+    if (L.kind != kAC && L.kind != kCH) return false;
+    if (L.ndim < 2 || !pow2(nx, 64, 8192) || !pow2(ny, 32, 4096)) return false;
+    return L.ndim == 2 || pow2(nz, 32, 4096);
+}
+
+hipError_t launch_fft_rows(const Launch &L, const void *args, const FftArgs &f, bool inverse, hipStream_t s)
+{
+    return L.fp32 ? launch_fft_rows_t(*static_cast<const StepArgs<float> *>(args), f, inverse, s)
+                  : launch_fft_rows_t(*static_cast<const StepArgs<double> *>(args), f, inverse, s);
+}
+
+int64_t fft_columns(bool fp32, int64_t nx)
+{
+    const int64_t cw = fp32 ? 8 : 4;  // kCw
+    return cdiv(nx / 2 + 1, cw) * cw;
+}
+
+hipError_t launch_fft_cols(const Launch &L, const SpecArgs &p, const FftArgs &f, int64_t n, bool along_z,
+                           int64_t batches, int mode, hipStream_t s)
+{
+    return L.fp32 ? launch_fft_cols_t<float>(p, f, n, along_z, batches, mode, s)
+                  : launch_fft_cols_t<double>(p, f, n, along_z, batches, mode, s);
+}
 
 hipError_t launch_spectral_nonlinear(const Launch &L, const void *args, void *g, hipStream_t s)
 {

@@ -202,6 +202,25 @@ struct SpecArgs {
 hipError_t launch_spectral_nonlinear(const Launch &L, const void *args, void *g, hipStream_t s);
 hipError_t launch_spectral_update(const Launch &L, const SpecArgs &a, hipStream_t s);
 
+// The library's own transforms of the spectral step (pf_fft.h), for 2D and 3D grids
+// whose extents are powers of two: nx from 64 to 8192, the others from 32 to 4096.
+struct FftArgs {
+    const void *twx, *tw;  // exp(-2 pi i k / n) of the rows' nx and of the column axis
+    const void *in;        // inverse rows: half spectra
+    void *out;             // forward rows: half spectra; columns: transformed in place
+    int64_t batch;         // distance of the planes of a half spectrum
+    int64_t stride;        // columns along z: distance of the values
+    int64_t cols;          // columns of a plane (padded), or values of a plane along z
+    int32_t op;            // rows: 0 the values, kAC / kCH the explicit term; update: kAC / kCH
+};
+// columns that a half spectrum of nx / 2 + 1 is padded to
+int64_t fft_columns(bool fp32, int64_t nx);
+bool own_fft_available(const Launch &L, int64_t nx, int64_t ny, int64_t nz);
+hipError_t launch_fft_rows(const Launch &L, const void *args, const FftArgs &f, bool inverse, hipStream_t s);
+// mode 0 forward, 1 inverse, 2 forward, update of p.uh, inverse
+hipError_t launch_fft_cols(const Launch &L, const SpecArgs &p, const FftArgs &f, int64_t n, bool along_z,
+                           int64_t batches, int mode, hipStream_t s);
+
 // Standalone reductions of the state buf[.][parity] (no step).
 hipError_t launch_reduce_state(const Launch &L, const void *args, hipStream_t s);
 int64_t reduce_partial_slots(int64_t nsites);
