@@ -25,7 +25,16 @@ namespace pf {
 
 namespace {
 
-constexpr int kMH3Items = 2048;  // work items a launch aims for (z chunks)
+// z chunks: about 2048 workgroups, at least 16 planes each
+int64_t usual_chunks(int64_t tiles, int64_t nz)
+{
+    return std::max<int64_t>(1, std::min<int64_t>(cdiv(2048, tiles), nz / 16));
+}
+constexpr int kMH3MarchSlots = 256;  // workgroups of the march that run at once (250 registers: one per CU)
+// of the column tiles: one per CU in FP64, two in FP32 (128^3 p2 FP64 in chunks for
+// two 38 us, for one 33 us)
+template <typename T>
+constexpr int kMH3TileSlots = sizeof(T) == 8 ? 256 : 512;
 
 // Output columns of a tile: 32 x 16.
 template <typename T, int R>
@@ -434,14 +443,14 @@ __global__ void __launch_bounds__((64 * MH3March<T, R>::NW)) k_mh3d_march(StepAr
 }
 
 // Launch geometry of the march: strips, outputs per strip, y tiles and z
-// chunks (at least 16 planes each, enough work items to fill the chip).
+// chunks.
 template <typename T, int R>
 bool plan_mh3d_march(StepArgs<T> &a)
 {
     using TL = MH3March<T, R>;
     const int64_t st = cdiv(a.nx, TL::OWMAX);
     const int64_t yt = cdiv(a.ny, TL::NR - 2 * TL::H);
-    const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(cdiv(kMH3Items, st * yt), a.nz / 16));
+    const int64_t chunks = best_chunks(st * yt, a.nz, TL::H, kMH3MarchSlots, usual_chunks(st * yt, a.nz));
     const int64_t clen = cdiv(a.nz, chunks);
     const int64_t items = st * yt * cdiv(a.nz, clen);
     if (items > (int64_t)INT32_MAX) return false;
@@ -485,9 +494,7 @@ hipError_t launch_mh3d(const Launch &L, const void *args, hipStream_t s)
                 using TL = MH3Tile<T, R>;
                 const int64_t tx = cdiv(a.nx, TL::TX), ty = cdiv(a.ny, TL::TY);
                 const int64_t tiles = tx * ty;
-                // z chunks: enough work items to fill the chip, at least 16 planes each
-                const int64_t chunks =
-                    std::max<int64_t>(1, std::min<int64_t>(cdiv(kMH3Items, tiles), a.nz / 16));
+                const int64_t chunks = best_chunks(tiles, a.nz, 2 * R, kMH3TileSlots<T>, usual_chunks(tiles, a.nz));
                 const int64_t clen = cdiv(a.nz, chunks);
                 const int64_t items = tiles * cdiv(a.nz, clen);
                 if (items > (int64_t)INT32_MAX || tx > INT32_MAX || ty > INT32_MAX) return;

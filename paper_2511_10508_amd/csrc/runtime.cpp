@@ -1169,7 +1169,10 @@ pf_status autotune(Model *m, int32_t trials)
     std::vector<int32_t> cand;
     const int32_t base[] = {16, 32, 64, 128, 256, 512, 1024};
     for (int32_t c : base)
-        if (c <= march * 2 || cand.empty()) cand.push_back((int32_t)std::min<int64_t>(c, march));
+        // long 3D marches: the whole-round chunks below stand in for the ends of the range
+        if (d.ndim == 3 && march >= 256 && (c < 32 || c > 256))
+            continue;
+        else if (c <= march * 2 || cand.empty()) cand.push_back((int32_t)std::min<int64_t>(c, march));
     std::sort(cand.begin(), cand.end());
     cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
     std::vector<int> tbs = {1};
@@ -1194,8 +1197,25 @@ pf_status autotune(Model *m, int32_t trials)
     if (two_pass_available(m->L) && !(d.flags & PF_FORCE_GENERIC)) forms.push_back({1, 2, 2});
     for (const auto &fm : forms) {
         const int tb = fm[0], rpw = fm[1], passes = fm[2];
+        std::vector<int32_t> lens = cand;
+        if (d.ndim == 3) {
+            // chunks that fill whole rounds of one or two workgroups per CU (384^3: 256
+            // tiles, three of 128 planes are one and a half rounds, two of 192 one)
+            m->tb = tb;
+            m->rpw_req = rpw;
+            m->passes_req = passes;
+            st = set_chunk(m, cand.front());
+            if (st != PF_OK) break;
+            const int64_t tiles = (int64_t)m->strips * m->ytiles;
+            for (int64_t slots : {256, 512, 1024, 1536}) {
+                const int64_t n = slots / std::max<int64_t>(1, tiles);
+                if (n < 1 || m->family != 0) continue;
+                const int32_t c = (int32_t)((march + n - 1) / n);
+                if (c >= 8 && std::find(lens.begin(), lens.end(), c) == lens.end()) lens.push_back(c);
+            }
+        }
         {
-            for (int32_t c : cand) {
+            for (int32_t c : lens) {
                 m->tb = tb;
                 m->rpw_req = d.ndim == 3 ? rpw : 0;
                 m->passes_req = passes;
