@@ -6,5 +6,7 @@ namespace pf {
 
 template hipError_t launch_deep2d_kind<float, kAC>(const Launch &, const StepArgs<float> &, const DeepPlan &, bool,
                                                  hipStream_t);
+template hipError_t launch_deep2d_batched_kind<float, kAC>(const Launch &, const BatchTable<float> &, int32_t, int32_t,
+                                                         int32_t, hipStream_t);
 
 }  // namespace pf

@@ -6,5 +6,7 @@ namespace pf {
 
 template hipError_t launch_deep2d_kind<double, kCH>(const Launch &, const StepArgs<double> &, const DeepPlan &, bool,
                                                  hipStream_t);
+template hipError_t launch_deep2d_batched_kind<double, kCH>(const Launch &, const BatchTable<double> &, int32_t, int32_t,
+                                                         int32_t, hipStream_t);
 
 }  // namespace pf

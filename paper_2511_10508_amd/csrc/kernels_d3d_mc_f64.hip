@@ -6,5 +6,7 @@ namespace pf {
 
 template hipError_t launch_deep3d_kind<double, kMC>(const Launch &, const StepArgs<double> &, const DeepPlan &, bool,
                                                  hipStream_t);
+template hipError_t launch_deep3d_batched_kind<double, kMC>(const Launch &, const BatchTable<double> &, int32_t, int32_t,
+                                                         int32_t, hipStream_t);
 
 }  // namespace pf

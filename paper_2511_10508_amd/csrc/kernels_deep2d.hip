@@ -131,6 +131,37 @@ int64_t deep2d_most_sites(const Launch &L, bool red)
     return two && !L.fp32 ? 2 * M : 7 * M / 2;
 }
 
+// Whole-chip time of a step: its waves' instructions over 1024 SIMDs, half as much
+// again for the barriers, and the tiles' loads at 2.4 TB/s (six requests of 3000^2,
+// estimated / measured us per step: Allen-Cahn p2 FP32 49 / 50, Gray-Scott p2 FP64
+// 181 / 184, Allen-Cahn p4 FP64 156 / 184).
+bool plan_deep2d_served(const Launch &L, int64_t nx, int64_t ny, Deep3Args *a, int32_t *tiles, double *work_us)
+{
+    bool ok = false;
+    dispatch_prec(L.fp32, [&](auto tz) {
+        using T = decltype(tz);
+        dispatch_kind(L.kind, [&](auto kc) {
+            constexpr int KIND = decltype(kc)::value;
+            dispatch_r(L.r, DeepRadii{}, [&](auto rc) {
+                constexpr int R = decltype(rc)::value;
+                using Tile = DeepServed<T, KIND, R>;
+                using D = DeepShape<T, KIND, R, Tile::W, Tile::LR>;
+                const int S = deep_served_steps(KIND, R), h = S * D::HS, TY = Tile::NWM * Tile::LR;
+                const int hx = nx == D::TX ? 0 : h, hy = ny == TY ? 0 : h;
+                const int64_t tx = cdiv(nx, D::TX - 2 * hx), ty = cdiv(ny, TY - 2 * hy);
+                if (tx * ty > (1 << 24)) return;
+                *a = Deep3Args{S, hx, hy, 0, (int32_t)cdiv(nx, tx), (int32_t)cdiv(ny, ty), 1, (int32_t)tx, (int32_t)ty};
+                *tiles = (int32_t)(tx * ty);
+                *work_us = (double)*tiles * (1.5 * Tile::NWM * Tile::LR * Tile::W * ops_per_site(KIND, R, L.fp32, false) *
+                                                 4 / 2400.0 / (4 * kCUs) +
+                                             (double)D::TX * TY * sizeof(T) * D::NF / 2.4e6 / S);
+                ok = true;
+            });
+        });
+    });
+    return ok;
+}
+
 hipError_t launch_deep2d(const Launch &L, const void *args, const DeepPlan &plan, int32_t steps, bool red,
                          hipStream_t s)
 {

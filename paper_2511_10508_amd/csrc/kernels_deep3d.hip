@@ -106,6 +106,44 @@ bool plan_deep3d(const Launch &L, int64_t nx, int64_t ny, int64_t nz, int64_t st
     return ok;
 }
 
+bool plan_deep2d_served(const Launch &L, int64_t nx, int64_t ny, Deep3Args *a, int32_t *tiles, double *work_us);
+
+bool plan_deep_served(const Launch &L, int64_t nx, int64_t ny, int64_t nz, Deep3Args *a, int32_t *tiles, double *work_us)
+{
+    if (L.ndim == 2) return plan_deep2d_served(L, nx, ny, a, tiles, work_us);
+    if (L.ndim != 3) return false;
+    bool ok = false;
+    dispatch_prec(L.fp32, [&](auto tz) {
+        using T = decltype(tz);
+        dispatch_kind(L.kind, [&](auto kc) {
+            constexpr int KIND = decltype(kc)::value;
+            dispatch_r(L.r, Deep3Radii{}, [&](auto rc) {
+                constexpr int R = decltype(rc)::value;
+                using V = Deep3Served<T, KIND, R>;
+                using Tile = typename V::tile;
+                constexpr int W = Tile::W, LZ = Tile::LZ;
+                using D = Deep3Shape<T, KIND, R, W, LZ>;
+                const int h = V::steps * D::HS, TX = D::TX, TY = 4 * V::waves;
+                const int hx = nx == TX ? 0 : (h + W - 1) / W * W, hy = ny == TY ? 0 : h;
+                const int64_t tx = cdiv(nx, TX - 2 * hx), ty = cdiv(ny, TY - 2 * hy), tzs = cdiv(nz, LZ - 2 * h);
+                if (tx * ty * tzs > (1 << 24)) return;
+                *a = Deep3Args{V::steps, hx, hy, h, (int32_t)(cdiv(cdiv(nx, tx), W) * W), (int32_t)cdiv(ny, ty),
+                               (int32_t)cdiv(nz, tzs), (int32_t)tx, (int32_t)ty};
+                *tiles = (int32_t)(tx * ty * tzs);
+                const bool tall = KIND == kCH && R == 2;
+                // instructions over 1024 SIMDs, and the bricks' loads at 2.4 TB/s (six requests
+                // of 200^3, estimated / measured us per step: Allen-Cahn p2 FP32 155 / 149,
+                // Gray-Scott p2 FP32 335 / 339, Gray-Scott p2 FP64 660 / 562)
+                *work_us = (double)*tiles * (V::waves * LZ * W * kOps[KIND - 1][R - 1][sizeof(T) == 8][0][tall] * 4 /
+                                                 2400.0 / (4 * kCUs) +
+                                             (double)TX * TY * LZ * sizeof(T) * D::NF / 2.4e6 / V::steps);
+                ok = true;
+            });
+        });
+    });
+    return ok;
+}
+
 // Thousands of sites up to which the bricks beat the (autotuned) marching
 // kernels, from both measured on 40^3 to 256^3: the marching kernels take about the
 // same time from 40^3 to 128^3 (FP32 Gray-Scott p2 24-26 us a step, bricks 3.6, 7.0,

@@ -1,6 +1,7 @@
 // Planning and dispatch of the 2D fused marching kernels (their launchers
 // are instantiated per precision and kind in kernels_f2d_*.hip).
 #include "pf_device.h"
+#include "pf_deep2d_kind.h"
 #include "pf_fused2d.h"
 
 namespace pf {
@@ -57,6 +58,16 @@ hipError_t launch_fused2d_batched(const Launch &L, const void *table, int32_t k,
                                   int tb, hipStream_t s)
 {
     hipError_t err = hipErrorInvalidValue;
+    if (tb >= kDeepBatch) {
+        dispatch_prec(L.fp32, [&](auto tz) {
+            using T = decltype(tz);
+            dispatch_kind(L.kind, [&](auto kc) {
+                err = launch_deep2d_batched_kind<T, decltype(kc)::value>(
+                    L, *static_cast<const BatchTable<T> *>(table), k, tb - kDeepBatch, blocks, s);
+            });
+        });
+        return err;
+    }
     if (tb == 2 && !time_block_available(L)) return err;
     dispatch_prec(L.fp32, [&](auto tz) {
         using T = decltype(tz);

@@ -1,5 +1,6 @@
 // Planning and dispatch of the 3D fused marching kernels (their launchers
 // are instantiated per precision and kind in kernels_f3d_*.hip).
+#include "pf_deep3d_kind.h"
 #include "pf_fused3d.h"
 
 namespace pf {
@@ -135,6 +136,16 @@ hipError_t launch_fused3d_batched(const Launch &L, const void *table, int32_t k,
                                   int tb, hipStream_t s)
 {
     hipError_t err = hipErrorInvalidValue;
+    if (tb >= kDeepBatch) {
+        dispatch_prec(L.fp32, [&](auto tz) {
+            using T = decltype(tz);
+            dispatch_kind(L.kind, [&](auto kc) {
+                err = launch_deep3d_batched_kind<T, decltype(kc)::value>(
+                    L, *static_cast<const BatchTable<T> *>(table), k, tb - kDeepBatch, blocks, s);
+            });
+        });
+        return err;
+    }
     if (tb == 2 && !time_block_available(L)) return err;
     dispatch_prec(L.fp32, [&](auto tz) {
         using T = decltype(tz);

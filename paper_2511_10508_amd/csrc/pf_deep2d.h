@@ -175,8 +175,8 @@ struct DeepShape {
     static_assert(R <= LR, "a wave's neighbours are the next waves");
 };
 
-template <typename T, int KIND, int R, int W, int LR, int NWM, bool RED>
-__global__ void __launch_bounds__(64 * NWM) k_deep2d(StepArgs<T> a, DeepArgs p)
+template <typename T, int KIND, int R, int W, int LR, bool RED>
+__device__ __forceinline__ void deep2d_tile(const StepArgs<T> &a, const DeepArgs &p, int par, int32_t tile)
 {
     using D = DeepShape<T, KIND, R, W, LR>;
     constexpr int TX = D::TX, NF = D::NF, SL = LR + R;
@@ -185,12 +185,11 @@ __global__ void __launch_bounds__(64 * NWM) k_deep2d(StepArgs<T> a, DeepArgs p)
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int NW = __builtin_amdgcn_readfirstlane((int)(blockDim.x >> 6));
     const int wu = w == 0 ? NW - 1 : w - 1, wd = w + 1 == NW ? 0 : w + 1;
-    const int32_t tile = xcd_item(blockIdx.x, gridDim.x);
     const int32_t ty = tile / p.tilesx, tx = tile - ty * p.tilesx;
     const int32_t nx = (int32_t)a.nx, ny = (int32_t)a.ny;
     const int32_t x0 = tx * p.ow - p.hx, y0 = ty * p.oh - p.hy + w * LR;  // first column, this wave's first row
     const int32_t xl = x0 + l * W;
-    const int par = a.parity, opar = par ^ 1;
+    const int opar = par ^ 1;
 
     // edge rows of wave v, stream f, buffer b: first R rows, then last R rows
     auto edge = [&](int b, int f, int v) {
@@ -501,6 +500,32 @@ __global__ void __launch_bounds__(64 * NWM) k_deep2d(StepArgs<T> a, DeepArgs p)
         write(std::true_type{});
     } else {
         write(std::false_type{});
+    }
+}
+
+template <typename T, int KIND, int R, int W, int LR, int NWM, bool RED>
+__global__ void __launch_bounds__(64 * NWM) k_deep2d(StepArgs<T> a, DeepArgs p)
+{
+    deep2d_tile<T, KIND, R, W, LR, RED>(a, p, a.parity, xcd_item(blockIdx.x, gridDim.x));
+}
+
+// Persistent batched form (see k_step2d_batched): S steps per launch of every
+// request that has steps left at step k of the tick, on tiles of one shape.  The
+// loop is uniform over the workgroup.
+template <typename T, int KIND, int R, int W, int LR, int NWM>
+__global__ void __launch_bounds__(64 * NWM) k_deep2d_batched(BatchTable<T> tb, int32_t k, int32_t S)
+{
+    const int32_t n = *tb.count;
+    const int32_t total = tb.item_start[n];
+    for (int32_t b = blockIdx.x; b < total; b += gridDim.x) {
+        const int32_t g = xcd_item(b, total);
+        const int i = __builtin_amdgcn_readfirstlane(batch_request(tb, n, g));
+        const int32_t left = tb.steps[i] - k;
+        if (left <= 0) continue;
+        const StepArgs<T> a = batch_args(tb, i, k / S);
+        const DeepArgs p{left < S ? left : S, a.deep.hx, a.deep.hy, a.deep.ow, a.deep.oh, a.deep.tilesx};
+        deep2d_tile<T, KIND, R, W, LR, false>(a, p, 0, g - tb.item_start[i]);
+        __syncthreads();  // the next tile reuses the LDS
     }
 }
 

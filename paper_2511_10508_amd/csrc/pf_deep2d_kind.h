@@ -45,6 +45,15 @@ struct DeepWideOf<double, KIND, R, RED> {
 template <typename T, int KIND, int R, bool RED>
 using DeepWide = typename DeepWideOf<T, KIND, R, RED>::type;
 
+// The batched launches: narrow tiles of eight waves (64 x 64 sites), as many
+// steps as leave 48 x 48 of them written.
+template <typename T, int KIND, int R>
+using DeepServed = DeepTile<1, 8, 8>;
+constexpr int deep_served_steps(int kind, int r) { return 8 / (kind == kCH ? 2 * r : r); }
+
+template <typename T, int KIND>
+hipError_t launch_deep2d_batched_kind(const Launch &L, const BatchTable<T> &t, int32_t k, int32_t S, int32_t blocks,
+                                      hipStream_t s);
 template <typename T, int KIND>
 hipError_t launch_deep2d_kind(const Launch &L, const StepArgs<T> &a, const DeepPlan &plan, bool red, hipStream_t s);
 

@@ -36,4 +36,21 @@ hipError_t launch_deep2d_kind(const Launch &L, const StepArgs<T> &a, const DeepP
     return err;
 }
 
+template <typename T, int KIND>
+hipError_t launch_deep2d_batched_kind(const Launch &L, const BatchTable<T> &t, int32_t k, int32_t S, int32_t blocks,
+                                      hipStream_t s)
+{
+    hipError_t err = hipErrorInvalidValue;
+    dispatch_r(L.r, DeepRadii{}, [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        using Tile = DeepServed<T, KIND, R>;
+        constexpr size_t lds = Tile::NWM * DeepShape<T, KIND, R, Tile::W, Tile::LR>::LDS_PER_WAVE;
+        if (S != deep_served_steps(KIND, R)) return;
+        hipLaunchKernelGGL((k_deep2d_batched<T, KIND, R, Tile::W, Tile::LR, Tile::NWM>), dim3(blocks),
+                           dim3(64 * Tile::NWM), lds, s, t, k, S);
+        err = hipGetLastError();
+    });
+    return err;
+}
+
 }  // namespace pf

@@ -60,9 +60,8 @@ struct Deep3Shape {
     static_assert(R <= W, "x-neighbours within the next lane");
 };
 
-template <typename T, int KIND, int R, int W, int LZ, int EU, bool RED>
-__global__ void __launch_bounds__(64 * kDeep3Waves) __attribute__((amdgpu_waves_per_eu(EU)))
-    k_deep3d(StepArgs<T> a, Deep3Args p)
+template <typename T, int KIND, int R, int W, int LZ, bool RED>
+__device__ __forceinline__ void deep3d_brick(const StepArgs<T> &a, const Deep3Args &p, int par, int32_t tile)
 {
     using D = Deep3Shape<T, KIND, R, W, LZ>;
     constexpr int TX = D::TX, NF = D::NF, SL = LZ + R;
@@ -72,12 +71,11 @@ __global__ void __launch_bounds__(64 * kDeep3Waves) __attribute__((amdgpu_waves_
     const int NW = __builtin_amdgcn_readfirstlane((int)(blockDim.x >> 6));
     const int TY = 4 * NW;
     const int ry = 4 * w + (l >> 4);  // row of the brick
-    const int32_t tile = xcd_item(blockIdx.x, gridDim.x);
     const int32_t tx = tile % p.tilesx, tyz = tile / p.tilesx, ty = tyz % p.tilesy, tz = tyz / p.tilesy;
     const int32_t nx = (int32_t)a.nx, ny = (int32_t)a.ny, nz = (int32_t)a.nz;
     const int32_t x0 = tx * p.ow - p.hx, y0 = ty * p.oh - p.hy, z0 = tz * p.od - p.hz;
     const int32_t xl = x0 + lx * W;
-    const int par = a.parity, opar = par ^ 1;
+    const int opar = par ^ 1;
     const int plane = TY * TX;
     T *lds = reinterpret_cast<T *>(deep_lds);
     // this lane's place in plane 0 of stream f, and its y-neighbours' rows
@@ -350,6 +348,33 @@ __global__ void __launch_bounds__(64 * kDeep3Waves) __attribute__((amdgpu_waves_
         write(std::true_type{});
     } else {
         write(std::false_type{});
+    }
+}
+
+template <typename T, int KIND, int R, int W, int LZ, int EU, bool RED>
+__global__ void __launch_bounds__(64 * kDeep3Waves) __attribute__((amdgpu_waves_per_eu(EU)))
+    k_deep3d(StepArgs<T> a, Deep3Args p)
+{
+    deep3d_brick<T, KIND, R, W, LZ, RED>(a, p, a.parity, xcd_item(blockIdx.x, gridDim.x));
+}
+
+// Persistent batched form, as k_deep2d_batched.
+template <typename T, int KIND, int R, int W, int LZ, int EU>
+__global__ void __launch_bounds__(64 * kDeep3Waves) __attribute__((amdgpu_waves_per_eu(EU)))
+    k_deep3d_batched(BatchTable<T> tb, int32_t k, int32_t S)
+{
+    const int32_t n = *tb.count;
+    const int32_t total = tb.item_start[n];
+    for (int32_t b = blockIdx.x; b < total; b += gridDim.x) {
+        const int32_t g = xcd_item(b, total);
+        const int i = __builtin_amdgcn_readfirstlane(batch_request(tb, n, g));
+        const int32_t left = tb.steps[i] - k;
+        if (left <= 0) continue;
+        const StepArgs<T> a = batch_args(tb, i, k / S);
+        Deep3Args p = a.deep;
+        p.steps = left < S ? left : S;
+        deep3d_brick<T, KIND, R, W, LZ, false>(a, p, 0, g - tb.item_start[i]);
+        __syncthreads();  // the next brick reuses the LDS
     }
 }
 

@@ -35,6 +35,22 @@ constexpr bool deep3d_built()
     return !(sizeof(T) == 8 && R == 2 && RED && KIND != kAC);
 }
 
+// The batched launches: flat bricks of four waves (32 x 16 x 8 sites, 28 x 12 x 4
+// written), tall ones of six for Cahn-Hilliard with r = 2.  Two fields with r = 2
+// keep two waves per SIMD: the arguments of a table entry stay in registers, and
+// at four they spill (132-388 B a lane).
+template <typename T, int KIND, int R>
+struct Deep3Served {
+    using tile = std::conditional_t<
+        KIND == kCH && R == 2, Deep3Tall<T, KIND, R, false>,
+        std::conditional_t<(KIND == kGS || KIND == kMC) && R == 2, Deep3Tile<2, 8, 2>, Deep3Flat<T, KIND, R, false>>>;
+    static constexpr int waves = KIND == kCH && R == 2 ? 6 : 4;
+    static constexpr int steps = KIND != kCH && R == 1 ? 2 : 1;
+};
+
+template <typename T, int KIND>
+hipError_t launch_deep3d_batched_kind(const Launch &L, const BatchTable<T> &t, int32_t k, int32_t S, int32_t blocks,
+                                      hipStream_t s);
 template <typename T, int KIND>
 hipError_t launch_deep3d_kind(const Launch &L, const StepArgs<T> &a, const DeepPlan &plan, bool red, hipStream_t s);
 

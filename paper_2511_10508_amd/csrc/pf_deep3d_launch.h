@@ -37,4 +37,22 @@ hipError_t launch_deep3d_kind(const Launch &L, const StepArgs<T> &a, const DeepP
     return err;
 }
 
+template <typename T, int KIND>
+hipError_t launch_deep3d_batched_kind(const Launch &L, const BatchTable<T> &t, int32_t k, int32_t S, int32_t blocks,
+                                      hipStream_t s)
+{
+    hipError_t err = hipErrorInvalidValue;
+    dispatch_r(L.r, Deep3Radii{}, [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        using V = Deep3Served<T, KIND, R>;
+        using Tile = typename V::tile;
+        constexpr size_t lds = V::waves * Deep3Shape<T, KIND, R, Tile::W, Tile::LZ>::LDS_PER_WAVE;
+        if (S != V::steps) return;
+        hipLaunchKernelGGL((k_deep3d_batched<T, KIND, R, Tile::W, Tile::LZ, Tile::EU>), dim3(blocks), dim3(64 * V::waves),
+                           lds, s, t, k, S);
+        err = hipGetLastError();
+    });
+    return err;
+}
+
 }  // namespace pf

@@ -31,6 +31,11 @@ constexpr int kWaves3D = 16;        // waves per workgroup of the 3D kernels (tw
 //   (AC, CH), q2 = number of non-finite values.  Each is an FP64 (hi, lo)
 //   pair; the runtime scales the sums by dx^d.
 
+// Deep tiles (see DeepPlan) of a brick; in 2D hz, od and tilesy are unused.
+struct Deep3Args {
+    int32_t steps, hx, hy, hz, ow, oh, od, tilesx, tilesy;
+};
+
 // Arguments of one model's step, shared by the single-model and batched
 // launches.  All sizes in elements.  Weights and constants are in the storage
 // precision T (rounded once from FP64 on the host).
@@ -59,6 +64,7 @@ struct StepArgs {
     double c1, c2;           // FP64 Landau constants (energy)
     double2 *part;           // partial sums [q][slot]
     int64_t pstride;         // slots per quantity
+    Deep3Args deep;          // served requests: their deep tiles in the batched launches
 };
 
 // Batched (serving) launch: a table of StepArgs, one per request of one
@@ -128,6 +134,9 @@ hipError_t launch_fused3d(const Launch &L, const void *args, int32_t blocks, int
 // with two or more steps left in the tick by a two-step sweep and those with
 // one left by a single step (their plan, made for two steps, covers the
 // single-step kernel); k counts steps, so the tick's launches are k = 0, 2, ..
+// tb = kDeepBatch + S: deep tiles, S steps per launch (a request with fewer left
+// takes those); the table's work items are the requests' deep tiles.
+constexpr int kDeepBatch = 64;
 hipError_t launch_fused2d_batched(const Launch &L, const void *table, int32_t k, int32_t blocks,
                                   int tb, hipStream_t s);
 hipError_t launch_fused3d_batched(const Launch &L, const void *table, int32_t k, int32_t blocks,
@@ -154,9 +163,6 @@ struct DeepArgs {
     int32_t tilesx;          // tiles along x
 };
 constexpr int kDeep3Waves = 8;      // the same of the 3D bricks (pf_deep3d.h)
-struct Deep3Args {
-    int32_t steps, hx, hy, hz, ow, oh, od, tilesx, tilesy;
-};
 struct DeepPlan {
     int32_t wide;            // tile shape: 0 the narrow (3D: flat), 1 the wide (tall) one of the kernel
     int32_t waves;           // waves per workgroup
@@ -172,6 +178,10 @@ struct DeepPlan {
 // estimated time per step; false where the family does not cover L.
 bool plan_deep2d(const Launch &L, int64_t nx, int64_t ny, int64_t steps, bool red, DeepPlan *plan);
 bool plan_deep3d(const Launch &L, int64_t nx, int64_t ny, int64_t nz, int64_t steps, bool red, DeepPlan *plan);
+// The one tile shape of L's batched (serving) launches: tiles and their arguments
+// (steps per launch among them), and the microseconds of the whole chip that a step
+// takes.  false where the family does not cover L.
+bool plan_deep_served(const Launch &L, int64_t nx, int64_t ny, int64_t nz, Deep3Args *a, int32_t *tiles, double *work_us);
 // Sites up to which deep tiles are faster than the marching kernels.
 int64_t deep2d_most_sites(const Launch &L, bool red);
 int64_t deep3d_most_sites(const Launch &L, bool red);

@@ -46,6 +46,13 @@ struct Model {
     StepArgs<double> a64{};
     StepArgs<float> a32{};
 
+    // served models: deep tiles of the batched launches (serve_tb steps per launch,
+    // 0: none), whole-chip microseconds they take per step
+    int serve_tb = 0;
+    int32_t serve_items = 0;
+    double serve_us = 0.0;
+    Deep3Args serve_deep{};
+
     double2 *part = nullptr;     // partial sums [kNumQ][pstride]
     int64_t pstride = 0;
     double2 *part2 = nullptr;    // second-level partials [kNumQ][kFinSlots]

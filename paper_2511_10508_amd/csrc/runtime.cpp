@@ -237,6 +237,7 @@ static void fill_args(Model *m, StepArgs<T> &a)
     a.c2 = (d.kind == kAC || d.kind == kCH) ? d.params[1] : 0.0;
     a.part = m->part;
     a.pstride = m->pstride;
+    a.deep = m->serve_deep;
 }
 
 // Plan the fused decomposition for the model's chunk length.
@@ -1001,6 +1002,9 @@ pf_status model_create(const pf_desc *desc, void *stream, void *const *bufs, int
         m->rpw_req = desc->ndim == 3 ? rows_per_wave_batched(m->L) : 2;
         m->passes_req = 1;
         m->tb = time_block_available(m->L) ? 2 : 1;
+        if (!(desc->flags & PF_FORCE_GENERIC) &&
+            plan_deep_served(m->L, desc->n[0], desc->n[1], desc->n[2], &m->serve_deep, &m->serve_items, &m->serve_us))
+            m->serve_tb = m->serve_deep.steps;
     }
     if (!m->async_alloc) {
         std::lock_guard<std::mutex> lk(g_tune_mu);

@@ -60,13 +60,15 @@ struct Req {
     uint64_t footprint = 0;
     int64_t finish_tick = -1;
     int cls = -1;            // batched class, -1 = stepped on its own
+    int dcls = -1;           // batched class on deep tiles, -1 = none
+    double march_us = 20.0;  // a step on its marching tiles alone (from the autotuner)
     double2 *pinned = nullptr;  // final reductions (slot of the server's pinned pool)
     int slot = -1;
     pf_result res{};
 };
 
 struct ClassKey {
-    int kind, ndim, r, fp32, tiny;
+    int kind, ndim, r, fp32, tiny;  // tiny: 1 whole grid in LDS, 2 deep tiles
     bool operator<(const ClassKey &o) const
     {
         return std::tie(kind, ndim, r, fp32, tiny) < std::tie(o.kind, o.ndim, o.r, o.fp32, o.tiny);
@@ -90,6 +92,7 @@ struct ClassTables {
     int32_t blocks[2] = {1, 1};          // persistent grid of this tick (power of two)
     int tb = 1;                          // steps per batched launch (2: two-step kernels)
     bool tiny = false;                   // whole grid in LDS, one launch per tick
+    bool deep = false;                   // deep tiles, tb steps per launch
     void *tune_dev = nullptr, *tune_host = nullptr;  // the autotuner's table (same layout)
     hipStream_t stream = nullptr;        // graph branch of this class
     hipEvent_t join = nullptr;
@@ -131,8 +134,8 @@ struct Server {
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t fork = nullptr;
     hipEvent_t tev[2] = {nullptr, nullptr};  // autotuner timing
-    // serving autotuner: chunk per (class, log2 of each extent)
-    std::map<std::tuple<int, int, int, int>, int32_t> tuned;
+    // serving autotuner: chunk and microseconds per step, per (class, log2 of each extent)
+    std::map<std::tuple<int, int, int, int>, std::pair<int32_t, double>> tuned;
     // written by the scheduler thread, read by pf_server_stats from any thread
     std::atomic<int64_t> tick{0}, launches{0}, captures{0}, replays{0};
     std::string fatal;  // guarded by mu (set_fatal)
@@ -153,18 +156,20 @@ static void set_fatal(Server *s, const std::string &msg)
     s->done_cv.notify_all();
 }
 
-static int class_of(Server *s, const Model *m)
+static int class_of(Server *s, const Model *m, bool deep = false)
 {
     const bool tiny = tiny_available(m->L, m->desc.n[0], m->desc.n[1], m->desc.n[2]);
     if (m->family != 0 && !tiny) return -1;
-    ClassKey k{m->L.kind, m->L.ndim, m->L.r, m->L.fp32, tiny ? 1 : 0};
+    if (deep && (tiny || m->serve_tb < 1)) return -1;
+    ClassKey k{m->L.kind, m->L.ndim, m->L.r, m->L.fp32, deep ? 2 : tiny ? 1 : 0};
     auto it = s->class_index.find(k);
     if (it != s->class_index.end()) return it->second;
     ClassTables t;
     t.key = k;
     t.L = m->L;
-    t.tb = m->tb;  // served models are planned for two-step sweeps where the class has them
+    t.tb = deep ? m->serve_tb : m->tb;  // (planned for two-step sweeps where the class has them)
     t.tiny = tiny;
+    t.deep = deep;
     const size_t argsz = m->fp32 ? sizeof(StepArgs<float>) : sizeof(StepArgs<double>);
     t.args_bytes = argsz * s->max_slots;
     const size_t total = t.args_bytes + sizeof(int32_t) * (2 * s->max_slots + 2);
@@ -238,14 +243,15 @@ static hipError_t launch_table(const ClassTables &t, int max_slots, void *dev, i
         BatchTable<double> tb{reinterpret_cast<StepArgs<double> *>(d), ints, ints + 1, ints + 1 + max_slots + 1};
         return launch_tiny(t.L, &tb, blocks, st);
     }
+    const int per = t.deep ? kDeepBatch + t.tb : t.tb;
     if (t.L.fp32) {
         BatchTable<float> tb{reinterpret_cast<StepArgs<float> *>(d), ints, ints + 1, ints + 1 + max_slots + 1};
-        return t.L.ndim == 2 ? launch_fused2d_batched(t.L, &tb, k, blocks, t.tb, st)
-                             : launch_fused3d_batched(t.L, &tb, k, blocks, t.tb, st);
+        return t.L.ndim == 2 ? launch_fused2d_batched(t.L, &tb, k, blocks, per, st)
+                             : launch_fused3d_batched(t.L, &tb, k, blocks, per, st);
     }
     BatchTable<double> tb{reinterpret_cast<StepArgs<double> *>(d), ints, ints + 1, ints + 1 + max_slots + 1};
-    return t.L.ndim == 2 ? launch_fused2d_batched(t.L, &tb, k, blocks, t.tb, st)
-                         : launch_fused3d_batched(t.L, &tb, k, blocks, t.tb, st);
+    return t.L.ndim == 2 ? launch_fused2d_batched(t.L, &tb, k, blocks, per, st)
+                         : launch_fused3d_batched(t.L, &tb, k, blocks, per, st);
 }
 
 // Launch the S batched steps of one class (buffer set `set`) on `st`: one
@@ -289,7 +295,7 @@ static int32_t fill_table(const ClassTables &t, int max_slots, void *host, const
             reinterpret_cast<StepArgs<double> *>(host)[i] = a;
         }
         start[i] = acc;
-        acc += m->items;
+        acc += t.deep ? m->serve_items : m->items;
         st[i] = steps[i];
     }
     start[ms.size()] = acc;
@@ -308,6 +314,10 @@ static int32_t persistent_blocks(const ClassTables &t, int64_t items)
         return b;
     }
     int32_t b = 1;
+    if (t.deep) {  // a workgroup per tile
+        while (b < items && b < 4096) b <<= 1;
+        return b;
+    }
     while (b < need && b < cap) b <<= 1;
     return b;
 }
@@ -345,7 +355,8 @@ static void tune_served(Server *s, Req *r)
     const auto key = std::make_tuple(r->cls, lg(d.n[0]), lg(d.n[1]), lg(d.n[2]));
     auto it = s->tuned.find(key);
     if (it != s->tuned.end()) {
-        if (it->second != m->clen) set_chunk(m, it->second);
+        if (it->second.first != m->clen) set_chunk(m, it->second.first);
+        r->march_us = it->second.second;
         return;
     }
     const int32_t keep = m->clen;
@@ -354,7 +365,7 @@ static void tune_served(Server *s, Req *r)
         const size_t total = t.args_bytes + sizeof(int32_t) * (2 * s->max_slots + 2);
         if (hipMalloc(&t.tune_dev, total) != hipSuccess ||
             hipHostMalloc(&t.tune_host, total, hipHostMallocDefault) != hipSuccess) {
-            s->tuned[key] = keep;
+            s->tuned[key] = {keep, r->march_us};
             return;
         }
     }
@@ -389,7 +400,8 @@ static void tune_served(Server *s, Req *r)
         }
     }
     if (set_chunk(m, best) != PF_OK) (void)set_chunk(m, keep);
-    s->tuned[key] = m->clen;
+    if (best_t < 1e300) r->march_us = best_t * (double)sites * 1e3 / 3;  // of three launches
+    s->tuned[key] = {m->clen, r->march_us};
 }
 
 // The graph of S chained batched launches of class c for table buffer `set`
@@ -460,15 +472,48 @@ static hipError_t run_classes(Server *s, const std::vector<int> &cls, int set, i
     return e;
 }
 
+// The classes whose requests run this tick on deep tiles, by the estimated times of
+// a step: a marching launch takes as long as its slowest request does alone until the
+// requests fill the chip; a deep launch has 6 us of its own and what its tiles load and
+// compute.  (The launches of different classes hardly overlap.)  Measured on one
+// class, marching / deep us per step: FP32 3D Gray-Scott p2, six of 64^3 39 / 21,
+// 128^3 124 / 97, 200^3 264 / 339; FP64 3D Cahn-Hilliard p2, six of 64^3 34 / 32,
+// 128^3 112 / 149; FP64 2D Allen-Cahn p4, six of 700^2 19 / 19, 3000^2 161 / 184.
+// The estimates are good to about 20 %, hence the 0.8; 2D with r = 1 was faster
+// on deep tiles at every size (300^2 to 3000^2, one and six requests, 1.3-2.9 times).
+// 24 mixed FP32 requests (2D to 512^2, 3D to 96^3) take 33 ms, 75 ms on marching tiles
+// alone; 64 of them 55 and 101 ms.
+static std::vector<char> deep_classes(Server *s, const std::vector<Req *> &run)
+{
+    struct Load {
+        double slowest = 0.0, sum = 0.0, deep = 0.0;
+    };
+    std::vector<Load> load(s->classes.size());
+    std::vector<char> deep(s->classes.size(), 0);
+    for (const Req *r : run) {
+        if (r->cls < 0 || r->dcls < 0) continue;
+        Load &l = load[r->cls];
+        const double part = r->m->items / (r->desc.ndim == 3 ? 150.0 : 1440.0);  // of the chip
+        // chained steps alone take about half as long again as the autotuner's launches
+        l.slowest = std::max(l.slowest, 1.5 * r->march_us);
+        l.sum += 1.2 * r->march_us * std::min(1.0, part);
+        if (l.deep == 0.0) l.deep = 6.0 / s->classes[r->dcls].tb;
+        l.deep += r->m->serve_us;
+        deep[r->cls] = (r->desc.ndim == 2 && r->m->L.r == 1) || l.deep < 0.8 * std::max(l.slowest, l.sum);
+    }
+    return deep;
+}
+
 // Enqueue one tick.  Returns false on a device error (recorded in fatal).
 static bool enqueue_tick(Server *s, std::vector<Req *> &run, int set)
 {
     const int S = s->spt;
     std::vector<std::vector<Req *>> by_class(s->classes.size());
     std::vector<Req *> solo;
+    const std::vector<char> deep = deep_classes(s, run);
     for (Req *r : run) {
         if (r->cls >= 0)
-            by_class[r->cls].push_back(r);
+            by_class[r->dcls >= 0 && deep[r->cls] ? r->dcls : r->cls].push_back(r);
         else
             solo.push_back(r);
     }
@@ -623,6 +668,7 @@ static void worker_main(Server *s)
                 (void)set_chunk(m, m->clen);
             }
             r->cls = class_of(s, m);
+            if (r->cls >= 0) r->dcls = class_of(s, m, true);
             r->state = RUNNING;
             s->active.push_back(r);  // a cancel during admission takes effect at the next tick
         }
