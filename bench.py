@@ -45,7 +45,7 @@ FAMILY_SOURCES = {"2d": ("pf_march2d.h", "pf_fused2d.h", "pf_fused2d_kind.h", "k
                   "mh2d": ("kernels_mh2d.hip",),
                   "mh3d": ("pf_march3d.h", "kernels_mh3d.hip"),
                   "chd3d": ("pf_march3d.h", "kernels_chd3d.hip"),
-                  "spectral": ("kernels_spectral.hip", "spectral.cpp")}
+                  "spectral": ("pf_fft.h", "pf_fft_launch.h", "kernels_spectral.hip", "spectral.cpp")}
 
 
 def source_hash(family="2d"):
@@ -210,7 +210,7 @@ def run_ch_variant(P, n, prec, steps, warmup, direct, ndim, seed=202):
 def run_spectral(P, n, prec, steps, warmup, seed=202):
     """Semi-implicit Fourier spectral Cahn-Hilliard (Eq. model-b) on a 2D n^2
     grid, dx = 1, dt = 0.5 (far above the explicit limit), c1 = c2 = 1, c0 =
-    U[-0.05, 0.05]: two hipFFT transforms (the updated spectrum is kept
+    U[-0.05, 0.05]: two transforms (the updated spectrum is kept
     between steps) and two element-wise kernels per step.  `per_site_bytes`
     is the scheme's minimum HBM traffic per site and step with these
     transforms (each transform reads and writes its data once, the

@@ -116,7 +116,8 @@ enum { PF_RED_MASS0 = 0, PF_RED_MASS1 = 1, PF_RED_ENERGY = 2, PF_RED_NONFINITE =
  *             about the separated states c^2 = c1/c2 (+inf for c1 = 0).  The
  *             mass reductions apply, the free energy is PF_ERR_UNSUPPORTED.
  *             The model holds two half spectra besides its fields (hipFFT
- *             plans allocate their own work space) and keeps the updated
+ *             plans, used where an extent is no power of two the library's own
+ *             transforms take, allocate their own work space) and keeps the updated
  *             spectrum between steps, so a run of steps takes two transforms
  *             per step; after pf_init, pf_set_field or pf_field_device the
  *             next step transforms the state again.  Not accepted by the server.

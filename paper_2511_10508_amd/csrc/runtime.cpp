@@ -1229,7 +1229,8 @@ pf_status autotune(Model *m, int32_t trials)
                 if (st != PF_OK) break;
                 // time `trials` launches; where they take less than kTuneMinMs,
                 // time again with enough launches to fill it (short launches
-                // differ by a few percent from one to the next)
+                // differ by a few percent from one to the next); not the ones that the
+                // first launches show to be far off
                 int reps = trials;
                 float ms = 0;
                 for (int pass = 0; pass < 2 && st == PF_OK; ++pass) {
@@ -1239,7 +1240,7 @@ pf_status autotune(Model *m, int32_t trials)
                     (void)hipEventRecord(b, m->stream);
                     (void)hipEventSynchronize(b);
                     (void)hipEventElapsedTime(&ms, a, b);
-                    if (pass > 0 || ms >= kTuneMinMs || !(ms > 0.f)) break;
+                    if (pass > 0 || ms >= kTuneMinMs || !(ms > 0.f) || ms > 1.3f * best * (float)(reps * tb)) break;
                     reps = std::min(64, (int)std::ceil(reps * kTuneMinMs / ms));
                 }
                 ms /= (float)reps * tb;
