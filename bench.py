@@ -308,10 +308,10 @@ def run_ch3d(P, n, order, prec, steps, warmup, seed=404):
 def run_ac128(P, steps=1000, seed=101):
     """The small workload: 2D Allen-Cahn 128^2, dx 1, dt 0.05, order 2, FP64,
     phi0 = U[-0.1, 0.1] (seed 101), 1000 steps: microseconds per step (wall)
-    of the default path, which runs the 1000 steps of a call in one
-    workgroup's LDS, eager and with PF_USE_GRAPH (the same launches), plus
-    the kernel time of one launch per step with HIP events (timing mode takes
-    that path)."""
+    of the default path, which runs up to 24 steps per launch on register
+    tiles, eager and with PF_USE_GRAPH (the same launches), plus the kernel
+    time per step of those launches by HIP events.  The names of the values
+    are older than that path."""
     out = {}
     for name, flags in (("lds", 0), ("lds_graph_flag", P.PF_USE_GRAPH)):
         d = P.make_desc(P.PF_AC, (128, 128), dx=1.0, dt=0.05, order=2, precision=P.PF_FP64,
