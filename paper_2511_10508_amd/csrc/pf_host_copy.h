@@ -8,16 +8,19 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 
 #include <hip/hip_runtime.h>
 
 namespace pf {
 
 // Two pinned halves, allocated on first use (as much as a transfer needs, at
-// most kHalf bytes each) and kept by their owner until release().  One transfer
-// at a time: the owner serialises.
+// most kHalf bytes each) and kept by their owner until release().  A transfer
+// holds `mu` from ensure() to its last use of the halves: its owner's other
+// threads would overwrite them, or free them to get larger ones.
 struct PinnedStage {
     static constexpr size_t kHalf = 4u << 20;
+    std::mutex mu;
     void *half[2] = {nullptr, nullptr};
     hipEvent_t ev[2] = {nullptr, nullptr};
     size_t bytes = 0;
@@ -70,6 +73,7 @@ inline void pitched_runs(int64_t e0, int64_t e1, int64_t nx, int64_t pitch, F &&
 inline hipError_t copy_field_out(PinnedStage &st, const void *dev, size_t ts, int64_t nx, int64_t rows, int64_t pitch,
                                  double *host, hipStream_t stream)
 {
+    std::lock_guard<std::mutex> lk(st.mu);
     const int64_t total = rows * pitch;
     hipError_t e = st.ensure((size_t)total * ts);
     const int64_t step = (int64_t)(st.bytes / ts);
@@ -104,6 +108,7 @@ inline hipError_t copy_field_out(PinnedStage &st, const void *dev, size_t ts, in
 inline hipError_t copy_field_in(PinnedStage &st, void *dev, size_t ts, int64_t nx, int64_t rows, int64_t pitch,
                                 const double *host, hipStream_t stream)
 {
+    std::lock_guard<std::mutex> lk(st.mu);
     const int64_t total = nx * rows;  // dense elements
     hipError_t e = st.ensure((size_t)total * ts);
     if (e != hipSuccess) return e;

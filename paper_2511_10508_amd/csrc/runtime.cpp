@@ -1473,6 +1473,7 @@ PF_API pf_status pf_get_window(pf_model *mm, int32_t field, const int64_t *origi
     // the window's sites gathered, wrapped and widened by a kernel into the pinned
     // halves, then to the caller
     const int64_t total = w[0] * w[1] * w[2];
+    std::lock_guard<std::mutex> lk(m->pin.mu);
     PF_HIP(m->pin.ensure((size_t)total * sizeof(double)), "hipHostMalloc(window)");
     const int64_t step = (int64_t)(m->pin.bytes / sizeof(double));
     WindowArgs a;

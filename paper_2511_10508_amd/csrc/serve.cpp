@@ -125,8 +125,7 @@ struct Server {
     double2 *pinned_pool = nullptr;  // max_slots x kNumQ result pairs (host-pinned)
     std::vector<int> free_slots;
 
-    std::mutex fetch_mu;    // one fetch at a time through the pinned halves
-    PinnedStage fetch_pin;
+    PinnedStage fetch_pin;  // of pf_server_fetch, one transfer at a time
 
     std::map<ClassKey, int> class_index;
     std::vector<ClassTables> classes;
@@ -855,7 +854,6 @@ PF_API pf_status pf_server_fetch(pf_server *ss, uint64_t ticket, int32_t field, 
     const pf_desc &d = m->desc;
     const int64_t N = d.n[0] * d.n[1] * d.n[2];
     if (count != N) return fail(PF_ERR_ARG, "count must equal the number of sites");
-    std::lock_guard<std::mutex> fl(s->fetch_mu);
     const hipError_t e = copy_field_out(s->fetch_pin, m->buf[field][m->parity], m->fp32 ? 4 : 8, d.n[0], d.n[1] * d.n[2],
                                         m->pitch, host, s->copy_stream);
     if (e != hipSuccess) return hip_fail(e, "fetch");
