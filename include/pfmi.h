@@ -264,9 +264,9 @@ pf_status pf_step(pf_model *m, int64_t nsteps);
  * pf_buffer_elems(desc) elements, 16-byte aligned; dev_bufs[2 f + p] is
  * buffer p of field f), starting from buffer `parity` (0 or 1) of every
  * field; the result is in buffer parity ^ (nsteps & 1).  The kernels and
- * their plan are those of a pf_create_on model with pf_set_tile(m, 0), one
- * step per launch and the default 3D tile layout, so fields and reductions
- * are bitwise that model's.  With PF_REDUCE_EACH_STEP, dev_history
+ * their plan are those of a pf_create_on model with pf_set_time_block(m, 1)
+ * (one step per launch, no register tiles), the default chunk and the default
+ * 3D tile layout, so fields and reductions are bitwise that model's.  With PF_REDUCE_EACH_STEP, dev_history
  * (caller-owned device memory of 6 * nsteps doubles) receives for step k the
  * reductions of the state at its start as three (hi, lo) pairs: the sum of
  * field 0, the sum of field 1 (GS, MC) or of the energy density (AC, CH),
@@ -320,10 +320,12 @@ pf_status pf_stream(pf_model *m, void **hip_stream);
  * Tile shape of the step kernels: chunk = sites marched per work item along
  * the slowest axis (y in 2D, z in 3D), 0 = the library's choice.  Fields
  * do not depend on it (bitwise); fused reductions agree to their compensated
- * accuracy (the partition into partial sums changes).  A chunk > 0, like
- * pf_set_time_block, makes pf_step take this tile (Allen-Cahn grids of at most
- * 128^2 sites without per-step reductions excepted).  pf_get_tile reports the current one and
- * the kernel family in use (0 fused marching, 1 per-site generic).
+ * accuracy (the partition into partial sums changes).  A chunk > 0 makes
+ * pf_step take this tile and no register tiles (2D Allen-Cahn grids of at most
+ * 128^2 sites without per-step reductions excepted), as do pf_set_time_block,
+ * pf_set_tile_rows with rows > 0 and, for 3D Cahn-Hilliard, pf_set_passes; 0 (and
+ * rows = 0) takes that back.  pf_get_tile reports the chunk of the marching
+ * kernels and the kernel family in use (0 fused, 1 per-site generic, 2 spectral).
  */
 pf_status pf_set_tile(pf_model *m, int32_t chunk);
 pf_status pf_get_tile(pf_model *m, int32_t *chunk, int32_t *family);

@@ -34,10 +34,13 @@ struct Model {
     // 3D CH: mu in registers (1) or through `scratch` (2); requested (0: the
     // library's choice), in use
     int passes_req = 0, passes = 1;
-    // the caller chose a tile, time block, layout or pass count (or the
-    // autotuner found the marching kernels faster): no deep tiles
-    bool pinned = false;
-    bool tuned_deep = false;       // the autotuner found deep tiles faster, whatever the size
+    // what the caller chose (pf_set_tile, pf_set_time_block, pf_set_tile_rows,
+    // pf_set_passes), and what the autotuner found fastest
+    bool pin_tile = false, pin_tb = false, pin_rows = false, pin_passes = false;
+    enum Tuned { kUntuned, kTunedMarching, kTunedDeep };
+    Tuned tuned = kUntuned;
+    // the marching kernels as planned: no deep tiles
+    bool pinned() const { return pin_tile || pin_tb || pin_rows || pin_passes || tuned == kTunedMarching; }
     double2 *deep_part = nullptr;  // reduction partials of several deep-tile launches
     int64_t deep_part_cap = 0;
     int32_t clen = 0, strips = 0, ow = 0, ytiles = 1, chunks = 0, items = 0, blocks = 0,

@@ -637,16 +637,17 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
 
 // Whether a call of nsteps steps runs on deep tiles, and its plan: up to the size
 // where the marching kernels overtake them (deep2d_most_sites), or where the
-// autotuner measured them faster.  Small Allen-Cahn grids take them even where the caller chose
-// a tile (a launch per step costs ten times as much there), except for
-// per-step reductions, whose partition the tile defines.
+// autotuner measured them faster, and not where the caller chose a tile, time
+// block, layout or pass count.  Small Allen-Cahn grids take them even then (a launch
+// per step costs ten times as much there), except for per-step reductions, whose
+// partition the tile defines.
 static bool deep_plan(const Model *m, int64_t nsteps, bool red, DeepPlan *plan)
 {
     const pf_desc &d = m->desc;
     if (m->family != 0 || d.ndim < 2 || nsteps < 1) return false;
     const int64_t N = d.n[0] * d.n[1] * d.n[2];
-    if (m->pinned && (red || d.kind != PF_AC || d.ndim != 2 || N > 128 * 128)) return false;
-    if (!m->tuned_deep && N > (d.ndim == 2 ? deep2d_most_sites(m->L, red) : deep3d_most_sites(m->L, red))) return false;
+    if (m->pinned() && (red || d.kind != PF_AC || d.ndim != 2 || N > 128 * 128)) return false;
+    if (m->tuned != Model::kTunedDeep && N > (d.ndim == 2 ? deep2d_most_sites(m->L, red) : deep3d_most_sites(m->L, red))) return false;
     return d.ndim == 2 ? plan_deep2d(m->L, d.n[0], d.n[1], nsteps, red, plan)
                        : plan_deep3d(m->L, d.n[0], d.n[1], d.n[2], nsteps, red, plan);
 }
@@ -1014,8 +1015,7 @@ pf_status model_create(const pf_desc *desc, void *stream, void *const *bufs, int
             m->tb = it->second.tb;
             m->rpw_req = it->second.rpw;
             m->passes_req = it->second.passes;
-            m->pinned = !it->second.deep;
-            m->tuned_deep = it->second.deep;
+            m->tuned = it->second.deep ? Model::kTunedDeep : Model::kTunedMarching;
         }
     }
     st = set_chunk(m, chunk);
@@ -1255,8 +1255,8 @@ pf_status autotune(Model *m, int32_t trials)
     }
     // deep tiles, the same way (not with per-step reductions, which the chosen
     // tile partitions)
-    m->pinned = false;
-    m->tuned_deep = true;
+    m->pin_tile = m->pin_tb = m->pin_rows = m->pin_passes = false;
+    m->tuned = Model::kTunedDeep;
     DeepPlan dp;
     if (st == PF_OK && !red && deep_plan(m, 1 << 20, false, &dp)) {
         union {
@@ -1289,8 +1289,7 @@ pf_status autotune(Model *m, int32_t trials)
     (void)hipEventDestroy(b);
     if (scratch) (void)hipFree(scratch);
     if (st != PF_OK) return st;
-    m->pinned = !bestc.deep;
-    m->tuned_deep = bestc.deep;
+    m->tuned = bestc.deep ? Model::kTunedDeep : Model::kTunedMarching;
     m->tb = bestc.tb;
     m->rpw_req = bestc.rpw;
     m->passes_req = bestc.passes;
@@ -1582,7 +1581,7 @@ PF_API pf_status pf_set_tile(pf_model *m, int32_t chunk)
 {
     if (!m || chunk < 0) return fail(PF_ERR_ARG, "bad argument");
     PF_HIP(hipStreamSynchronize(M(m)->stream), "hipStreamSynchronize");
-    if (chunk > 0) M(m)->pinned = true;
+    M(m)->pin_tile = chunk > 0;
     return set_chunk(M(m), chunk);
 }
 
@@ -1602,7 +1601,7 @@ PF_API pf_status pf_set_time_block(pf_model *m, int32_t tb)
     if (tb == 2 && (!time_block_available(mm->L) || mm->desc.flags & PF_FORCE_GENERIC))
         return fail(PF_ERR_UNSUPPORTED, "two-step kernels exist for 2D orders 2 and 4 and 3D order 2");
     mm->tb = tb;
-    mm->pinned = true;
+    mm->pin_tb = true;
     pf_status st = set_chunk(mm, mm->clen);
     if (st == PF_OK && mm->tb != tb) return fail(PF_ERR_UNSUPPORTED, "two-step kernel not available");
     return st;
@@ -1621,6 +1620,7 @@ PF_API pf_status pf_set_tile_rows(pf_model *m, int32_t rows)
         return fail(PF_ERR_UNSUPPORTED, "one row per wave is built for FP64 AC (order <= 4) and GS (order 2), "
                                         "four for CH, Model C, GS (order >= 4) and AC (order 8)");
     mm->rpw_req = rows;
+    mm->pin_rows = rows > 0;
     return set_chunk(mm, mm->clen);
 }
 
@@ -1646,6 +1646,8 @@ PF_API pf_status pf_set_passes(pf_model *m, int32_t passes)
         mm->scratch = nullptr;
     }
     if (st == PF_OK && mm->passes != passes) return fail(PF_ERR_UNSUPPORTED, "two-pass kernels not available");
+    // a choice only where there is one (one pass is accepted for every model)
+    if (st == PF_OK && two_pass_available(mm->L)) mm->pin_passes = true;
     return st;
 }
 

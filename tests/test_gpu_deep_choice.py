@@ -1,0 +1,58 @@
+"""Which kernels a model steps on (the launches per step of pf_timing_read): deep
+tiles take several steps per launch, the marching kernels as planned here one."""
+import numpy as np
+import pytest
+
+import paper_2511_10508_amd as P
+
+pytestmark = pytest.mark.gpu
+
+STEPS = 24
+
+
+def _model(kind, n, order=2, prec=P.PF_FP32, flags=0):
+    params, dt = {P.PF_AC: ([1.0, 1.0], 0.02), P.PF_CH: ([1.0, 1.0], 0.004),
+                  P.PF_GS: ([0.2, 0.1, 0.04, 0.06], 0.3), P.PF_MC: ([1.0, 1.0, 0.5], 0.01)}[kind]
+    m = P.Model(P.make_desc(kind, n, dt=dt, order=order, precision=prec, params=params, flags=flags))
+    m.init(P.PF_IC_UNIFORM, 7, (-0.1, 0.1))
+    return m
+
+
+def _deep(m, steps=STEPS):
+    """Whether a call of `steps` steps ran on deep tiles."""
+    m.timing(True)
+    m.step(steps)
+    _, launches, done = m.timing_read()
+    m.timing(False)
+    assert done == steps
+    return launches < steps
+
+
+def test_a_chosen_layout_or_pass_count_is_taken():
+    m = _model(P.PF_GS, (40, 30, 20))
+    assert _deep(m)
+    m.set_tile_rows(2)
+    assert not _deep(m)
+    m.set_tile_rows(0)
+    assert _deep(m)
+    m = _model(P.PF_CH, (40, 30, 20))
+    assert _deep(m)
+    m.set_passes(2)
+    assert m.passes() == 2 and not _deep(m)
+    m.set_passes(1)
+    assert m.passes() == 1 and not _deep(m)
+
+
+def test_a_chosen_tile_is_taken_until_the_choice_is_given_back():
+    m = _model(P.PF_CH, (200, 150))
+    assert _deep(m)
+    m.set_passes(1)  # no choice in 2D
+    assert _deep(m)
+    m.set_tile(16)
+    assert not _deep(m)
+    m.set_tile(0)
+    assert _deep(m)
+    m.set_time_block(1)
+    assert not _deep(m)
+    m.set_tile(0)  # the time block stays
+    assert not _deep(m)
