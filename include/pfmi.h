@@ -325,7 +325,9 @@ pf_status pf_stream(pf_model *m, void **hip_stream);
  * 128^2 sites without per-step reductions excepted), as do pf_set_time_block,
  * pf_set_tile_rows with rows > 0 and, for 3D Cahn-Hilliard, pf_set_passes; 0 (and
  * rows = 0) takes that back.  pf_get_tile reports the chunk of the marching
- * kernels and the kernel family in use (0 fused, 1 per-site generic, 2 spectral).
+ * kernels and the kernel family in use (0 fused, 1 per-site generic, 2 spectral);
+ * for a model that pf_autotune put on register tiles the chunk is 0, the time block
+ * 1 and the tile rows 0.
  */
 pf_status pf_set_tile(pf_model *m, int32_t chunk);
 pf_status pf_get_tile(pf_model *m, int32_t *chunk, int32_t *family);
@@ -383,12 +385,13 @@ int32_t pf_get_passes(const pf_model *m);
 
 /*
  * Autotuner: times each candidate (chunk length, time-block factor, 3D tile
- * layout, passes of a 3D Cahn-Hilliard step; for 2D models without per-step
- * reductions also the register tiles of pf_step) on the model's own buffers by re-running steps from the current
- * state (whose buffer is never written, so the state is unchanged), keeps the
- * fastest per step and records it in an in-process cache keyed by (kind,
+ * layout, passes of a 3D Cahn-Hilliard step, and the register tiles of pf_step)
+ * on the model's own buffers by re-running steps from the current state (whose
+ * buffer is never written, so the state is unchanged), keeps the fastest per
+ * step in place of what pf_set_tile and its like chose, and records it in an in-process cache keyed by (kind,
  * ndim, order, precision, per-step reductions, size class) that later models
- * of the same class reuse.
+ * of the same class reuse.  Register tiles are timed for models with per-step
+ * reductions only at the sizes where pf_step takes them by itself.
  * trials = timed launches per candidate (<= 0: 3); where they take less
  * than 2 ms, the candidate is timed again with as many launches as fill
  * 2 ms (at most 64).

@@ -327,7 +327,8 @@ int32_t default_chunk(const pf_desc *d)
 struct TuneChoice {
     int32_t chunk;
     int tb, rpw, passes;
-    bool deep;  // deep tiles beat every marching candidate
+    bool deep;      // deep tiles beat every marching candidate
+    int64_t sites;  // of the grid it was measured on
 };
 using TuneKey = std::tuple<int, int, int, int, int, int, int, int>;
 static std::mutex g_tune_mu;
@@ -636,8 +637,10 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
 }
 
 // Whether a call of nsteps steps runs on deep tiles, and its plan: up to the size
-// where the marching kernels overtake them (deep2d_most_sites), or where the
-// autotuner measured them faster, and not where the caller chose a tile, time
+// where the marching kernels overtake them (deep2d_most_sites), or, without
+// per-step reductions, where the autotuner measured them faster (with them the
+// choice, and so the partition of the sums, stays the one that any model with
+// pf_set_tile(m, 0) makes), and not where the caller chose a tile, time
 // block, layout or pass count.  Small Allen-Cahn grids take them even then (a launch
 // per step costs ten times as much there), except for per-step reductions, whose
 // partition the tile defines.
@@ -647,7 +650,7 @@ static bool deep_plan(const Model *m, int64_t nsteps, bool red, DeepPlan *plan)
     if (m->family != 0 || d.ndim < 2 || nsteps < 1) return false;
     const int64_t N = d.n[0] * d.n[1] * d.n[2];
     if (m->pinned() && (red || d.kind != PF_AC || d.ndim != 2 || N > 128 * 128)) return false;
-    if (m->tuned != Model::kTunedDeep && N > (d.ndim == 2 ? deep2d_most_sites(m->L, red) : deep3d_most_sites(m->L, red))) return false;
+    if ((red || m->tuned != Model::kTunedDeep) && N > (d.ndim == 2 ? deep2d_most_sites(m->L, red) : deep3d_most_sites(m->L, red))) return false;
     return d.ndim == 2 ? plan_deep2d(m->L, d.n[0], d.n[1], nsteps, red, plan)
                        : plan_deep3d(m->L, d.n[0], d.n[1], d.n[2], nsteps, red, plan);
 }
@@ -1015,7 +1018,11 @@ pf_status model_create(const pf_desc *desc, void *stream, void *const *bufs, int
             m->tb = it->second.tb;
             m->rpw_req = it->second.rpw;
             m->passes_req = it->second.passes;
-            m->tuned = it->second.deep ? Model::kTunedDeep : Model::kTunedMarching;
+            // deep tiles lose with size: a finding for them holds for smaller grids
+            // of the class, one against them for larger ones
+            const int64_t N = desc->n[0] * desc->n[1] * desc->n[2];
+            if (it->second.deep ? N <= it->second.sites : N >= it->second.sites)
+                m->tuned = it->second.deep ? Model::kTunedDeep : Model::kTunedMarching;
         }
     }
     st = set_chunk(m, chunk);
@@ -1156,8 +1163,8 @@ pf_status init_fields(Model *m, int32_t ic, uint64_t seed, const double *p, int3
     return PF_OK;
 }
 
-// Times every candidate (chunk length, time-block factor) on the model's own
-// buffers: each trial re-runs steps from the current parity, whose buffer is
+// Times every candidate (chunk length, time-block factor, 3D layout, passes, deep
+// tiles) on the model's own buffers: each trial re-runs steps from the current parity, whose buffer is
 // never written, so the state is untouched.  Keeps the fastest per step.
 constexpr float kTuneMinMs = 2.0f;  // least timed span per autotuner candidate
 
@@ -1184,13 +1191,34 @@ pf_status autotune(Model *m, int32_t trials)
     if (trials < 1) trials = 3;
     const int32_t keep_c = m->clen;
     const int keep_tb = m->tb, keep_rpw = m->rpw_req, keep_passes = m->passes_req;
+    const Model::Tuned keep_tuned = m->tuned;
+    const bool keep_pins[4] = {m->pin_tile, m->pin_tb, m->pin_rows, m->pin_passes};
     hipEvent_t a, b;
     PF_HIP(hipEventCreate(&a), "hipEventCreate");
     PF_HIP(hipEventCreate(&b), "hipEventCreate");
-    double2 *scratch = nullptr;
-    if (red) PF_HIP(hipMalloc((void **)&scratch, sizeof(double2) * kNumQ * 2), "hipMalloc(tune)");
     float best = 1e30f;
-    TuneChoice bestc{keep_c, keep_tb, keep_rpw, keep_passes, false};
+    const int64_t N = d.n[0] * d.n[1] * d.n[2];
+    TuneChoice bestc{keep_c, keep_tb, keep_rpw, keep_passes, false, N};
+    // Milliseconds per step of `launch`, `per` steps each: `trials` launches; where
+    // they take less than kTuneMinMs, again with enough launches to fill it (short
+    // launches differ by a few percent from one to the next); not the ones that the
+    // first launches show to be far off.
+    auto time_steps = [&](auto &&launch, int per, float *out) {
+        pf_status st = launch();
+        int reps = trials;
+        float ms = 0;
+        for (int pass = 0; pass < 2 && st == PF_OK; ++pass) {
+            (void)hipEventRecord(a, m->stream);
+            for (int t = 0; t < reps && st == PF_OK; ++t) st = launch();
+            (void)hipEventRecord(b, m->stream);
+            (void)hipEventSynchronize(b);
+            (void)hipEventElapsedTime(&ms, a, b);
+            if (pass > 0 || ms >= kTuneMinMs || !(ms > 0.f) || ms > 1.3f * best * (float)(reps * per)) break;
+            reps = std::min(64, (int)std::ceil(reps * kTuneMinMs / ms));
+        }
+        *out = ms / ((float)reps * per);
+        return st;
+    };
     pf_status st = PF_OK;
     // (tb, rpw, passes): every time block and 3D tile layout in one pass, and
     // the two-pass form where it exists
@@ -1218,77 +1246,80 @@ pf_status autotune(Model *m, int32_t trials)
                 if (c >= 8 && std::find(lens.begin(), lens.end(), c) == lens.end()) lens.push_back(c);
             }
         }
-        {
-            for (int32_t c : lens) {
-                m->tb = tb;
-                m->rpw_req = d.ndim == 3 ? rpw : 0;
-                m->passes_req = passes;
-                st = set_chunk(m, c);
-                if (st != PF_OK || m->family != 0 || m->tb != tb || m->passes != passes) break;
-                st = launch_step(m, m->parity, red, scratch, false, tb);
-                if (st != PF_OK) break;
-                // time `trials` launches; where they take less than kTuneMinMs,
-                // time again with enough launches to fill it (short launches
-                // differ by a few percent from one to the next); not the ones that the
-                // first launches show to be far off
-                int reps = trials;
-                float ms = 0;
-                for (int pass = 0; pass < 2 && st == PF_OK; ++pass) {
-                    (void)hipEventRecord(a, m->stream);
-                    for (int t = 0; t < reps && st == PF_OK; ++t)
-                        st = launch_step(m, m->parity, red, scratch, false, tb);
-                    (void)hipEventRecord(b, m->stream);
-                    (void)hipEventSynchronize(b);
-                    (void)hipEventElapsedTime(&ms, a, b);
-                    if (pass > 0 || ms >= kTuneMinMs || !(ms > 0.f) || ms > 1.3f * best * (float)(reps * tb)) break;
-                    reps = std::min(64, (int)std::ceil(reps * kTuneMinMs / ms));
-                }
-                ms /= (float)reps * tb;
-                if (st == PF_OK && ms < best) {
-                    best = ms;
-                    bestc = {c, tb, m->rpw_req, passes, false};
-                }
-            }
+        for (int32_t c : lens) {
+            m->tb = tb;
+            m->rpw_req = d.ndim == 3 ? rpw : 0;
+            m->passes_req = passes;
+            st = set_chunk(m, c);
+            if (st != PF_OK || m->family != 0 || m->tb != tb || m->passes != passes) break;
+            // reductions as pf_step takes them: partials, finalised many steps at a time
+            float ms = 0;
+            st = time_steps([&] { return launch_step(m, m->parity, red, nullptr, false, tb, red ? m->part : nullptr); },
+                            tb, &ms);
             if (st != PF_OK) break;
+            if (ms < best) {
+                best = ms;
+                bestc = {c, tb, m->rpw_req, passes, false, N};
+            }
         }
         if (st != PF_OK) break;
     }
-    // deep tiles, the same way (not with per-step reductions, which the chosen
-    // tile partitions)
+    // deep tiles, the same way (not where their partials find no memory)
     m->pin_tile = m->pin_tb = m->pin_rows = m->pin_passes = false;
     m->tuned = Model::kTunedDeep;
     DeepPlan dp;
-    if (st == PF_OK && !red && deep_plan(m, 1 << 20, false, &dp)) {
+    if (st == PF_OK && deep_plan(m, 1 << 20, red, &dp)) {
         union {
             StepArgs<double> d64;
             StepArgs<float> d32;
         } u;
-        if (m->fp32) {
-            u.d32 = m->a32;
-            u.d32.parity = m->parity;
-        } else {
-            u.d64 = m->a64;
-            u.d64.parity = m->parity;
+        double2 *part = nullptr;
+        const int64_t slots = dp.slots();
+        if (red && hipMalloc((void **)&part, sizeof(double2) * kNumQ * slots * dp.steps) != hipSuccess) {
+            (void)hipGetLastError();
+            part = nullptr;
         }
-        hipError_t e = launch_deep(m, &u, dp, dp.steps, false);
-        int reps = trials;
-        float ms = 0;
-        for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
-            (void)hipEventRecord(a, m->stream);
-            for (int t = 0; t < reps && e == hipSuccess; ++t) e = launch_deep(m, &u, dp, dp.steps, false);
-            (void)hipEventRecord(b, m->stream);
-            (void)hipEventSynchronize(b);
-            (void)hipEventElapsedTime(&ms, a, b);
-            if (pass > 0 || ms >= kTuneMinMs || !(ms > 0.f)) break;
-            reps = std::min(64, (int)std::ceil(reps * kTuneMinMs / ms));
+        auto set = [&](auto &to, const auto &from) {
+            to = from;
+            to.parity = m->parity;
+            if (red) {
+                to.part = part;
+                to.pstride = slots;
+            }
+        };
+        if (m->fp32)
+            set(u.d32, m->a32);
+        else
+            set(u.d64, m->a64);
+        if (!red || part) {
+            float ms = 0;
+            st = time_steps(
+                [&] {
+                    const hipError_t e = launch_deep(m, &u, dp, dp.steps, red);
+                    return e == hipSuccess ? PF_OK : hip_fail(e, "deep-tile step launch");
+                },
+                dp.steps, &ms);
+            bestc.deep = st == PF_OK && ms < best;
         }
-        if (e != hipSuccess) st = hip_fail(e, "deep-tile step launch");
-        bestc.deep = st == PF_OK && ms / ((float)reps * dp.steps) < best;
+        if (part) {
+            (void)hipStreamSynchronize(m->stream);
+            (void)hipFree(part);
+        }
     }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
-    if (scratch) (void)hipFree(scratch);
-    if (st != PF_OK) return st;
+    if (st != PF_OK) {  // the model as it was
+        m->tb = keep_tb;
+        m->rpw_req = keep_rpw;
+        m->passes_req = keep_passes;
+        m->tuned = keep_tuned;
+        m->pin_tile = keep_pins[0];
+        m->pin_tb = keep_pins[1];
+        m->pin_rows = keep_pins[2];
+        m->pin_passes = keep_pins[3];
+        (void)set_chunk(m, keep_c);
+        return st;
+    }
     m->tuned = bestc.deep ? Model::kTunedDeep : Model::kTunedMarching;
     m->tb = bestc.tb;
     m->rpw_req = bestc.rpw;
@@ -1588,7 +1619,7 @@ PF_API pf_status pf_set_tile(pf_model *m, int32_t chunk)
 PF_API pf_status pf_get_tile(pf_model *m, int32_t *chunk, int32_t *family)
 {
     if (!m) return fail(PF_ERR_ARG, "model is NULL");
-    if (chunk) *chunk = M(m)->clen;
+    if (chunk) *chunk = M(m)->on_deep() ? 0 : M(m)->clen;
     if (family) *family = M(m)->family;
     return PF_OK;
 }
@@ -1607,7 +1638,12 @@ PF_API pf_status pf_set_time_block(pf_model *m, int32_t tb)
     return st;
 }
 
-PF_API int32_t pf_get_time_block(const pf_model *m) { return m ? reinterpret_cast<const Model *>(m)->tb : -1; }
+PF_API int32_t pf_get_time_block(const pf_model *m)
+{
+    if (!m) return -1;
+    const Model *mm = reinterpret_cast<const Model *>(m);
+    return mm->on_deep() ? 1 : mm->tb;
+}
 
 PF_API pf_status pf_set_tile_rows(pf_model *m, int32_t rows)
 {
@@ -1628,7 +1664,7 @@ PF_API int32_t pf_get_tile_rows(const pf_model *m)
 {
     if (!m) return -1;
     const Model *mm = reinterpret_cast<const Model *>(m);
-    return (mm->desc.ndim == 3 && mm->family == 0) ? mm->rpw : 0;
+    return (mm->desc.ndim == 3 && mm->family == 0 && !mm->on_deep()) ? mm->rpw : 0;
 }
 
 PF_API pf_status pf_set_passes(pf_model *m, int32_t passes)

@@ -1,5 +1,5 @@
 """Which kernels a model steps on (the launches per step of pf_timing_read): deep
-tiles take several steps per launch, the marching kernels as planned here one."""
+tiles take more of them than the time block of the marching kernels."""
 import numpy as np
 import pytest
 
@@ -25,7 +25,7 @@ def _deep(m, steps=STEPS):
     _, launches, done = m.timing_read()
     m.timing(False)
     assert done == steps
-    return launches < steps
+    return launches < -(-steps // m.time_block())
 
 
 def test_a_chosen_layout_or_pass_count_is_taken():
@@ -56,3 +56,29 @@ def test_a_chosen_tile_is_taken_until_the_choice_is_given_back():
     assert not _deep(m)
     m.set_tile(0)  # the time block stays
     assert not _deep(m)
+
+
+@pytest.mark.parametrize("kind,n,order,prec", [(P.PF_CH, (1024, 1024), 4, P.PF_FP64),
+                                               (P.PF_GS, (96, 96, 96), 2, P.PF_FP32)])
+def test_autotuned_models_with_reductions_stay_on_deep_tiles_where_faster(kind, n, order, prec):
+    """Deep tiles take half the marching kernels' time or less at these sizes: the
+    tuned model keeps them, and so does a later model of its class."""
+    red = P.PF_REDUCE_EACH_STEP
+    m = _model(kind, n, order, prec, red)
+    assert _deep(m)
+    before = [m.get_field(f) for f in range(m.desc.nfields)]
+    m.autotune(2)
+    for f, a in enumerate(before):
+        assert np.array_equal(m.get_field(f), a)
+    assert m.tile()[0] == 0 and m.time_block() == 1 and m.tile_rows() == 0
+    assert _deep(m)
+    m.set_tile(16)
+    assert m.tile()[0] == 16 and not _deep(m)
+    assert _deep(_model(kind, n, order, prec, red))
+    # the history of a tuned model: as in the marching kernels' partition
+    a, b = _model(kind, n, order, prec, red), _model(kind, n, order, prec, red)
+    b.set_tile(16)
+    for x in (a, b):
+        x.step(STEPS)
+    u, v = a.reduce_history(P.PF_RED_MASS0, STEPS), b.reduce_history(P.PF_RED_MASS0, STEPS)
+    assert np.max(np.abs((u[0] + u[1]) - (v[0] + v[1]))) <= 1e-15 * a.nsites
