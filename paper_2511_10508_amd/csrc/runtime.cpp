@@ -1164,9 +1164,15 @@ pf_status init_fields(Model *m, int32_t ic, uint64_t seed, const double *p, int3
 }
 
 // Times every candidate (chunk length, time-block factor, 3D layout, passes, deep
-// tiles) on the model's own buffers: each trial re-runs steps from the current parity, whose buffer is
-// never written, so the state is untouched.  Keeps the fastest per step.
-constexpr float kTuneMinMs = 2.0f;  // least timed span per autotuner candidate
+// tiles): each trial runs steps from the current buffer, which is never written, so
+// the state is untouched, into the model's other one and on between that and a
+// temporary third, as pf_step alternates two.  Reading the same buffer every time
+// leaves it in the caches clean: 4096^2 Gray-Scott p4 FP64 then came out faster on
+// marching tiles, where pf_step takes 66 us a step, than on deep ones, 51 us.  Where two sets
+// of buffers exceed kTuneThirdBytes (four times the last-level cache) or the third
+// finds no memory, every trial reads the current one.  Keeps the fastest per step.
+constexpr float kTuneMinMs = 2.0f;                  // least timed span per autotuner candidate
+constexpr int64_t kTuneThirdBytes = 1ll << 30;
 
 pf_status autotune(Model *m, int32_t trials)
 {
@@ -1199,17 +1205,36 @@ pf_status autotune(Model *m, int32_t trials)
     float best = 1e30f;
     const int64_t N = d.n[0] * d.n[1] * d.n[2];
     TuneChoice bestc{keep_c, keep_tb, keep_rpw, keep_passes, false, N};
+    const int64_t field_bytes = (int64_t)tsize(m) * m->elems;
+    char *third = nullptr;
+    if (2 * m->nf * field_bytes <= kTuneThirdBytes && hipMalloc((void **)&third, m->nf * field_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        third = nullptr;
+    }
+    // launch k of a candidate reads buffer 0 and writes buffer 1 of these arguments
+    auto point = [&](auto &args, int64_t k) {
+        using T = std::remove_pointer_t<std::remove_reference_t<decltype(args.buf[0][0])>>;
+        for (int f = 0; f < kMaxFields; ++f) {
+            const int g = f < m->nf ? f : 0;
+            T *now = static_cast<T *>(m->buf[g][m->parity]), *other = static_cast<T *>(m->buf[g][m->parity ^ 1]);
+            T *spare = third ? reinterpret_cast<T *>(third + g * field_bytes) : nullptr;
+            args.buf[f][0] = k == 0 || !third ? now : k & 1 ? other : spare;
+            args.buf[f][1] = k == 0 || !third ? other : k & 1 ? spare : other;
+        }
+        args.parity = 0;
+    };
     // Milliseconds per step of `launch`, `per` steps each: `trials` launches; where
     // they take less than kTuneMinMs, again with enough launches to fill it (short
     // launches differ by a few percent from one to the next); not the ones that the
     // first launches show to be far off.
     auto time_steps = [&](auto &&launch, int per, float *out) {
-        pf_status st = launch();
+        int64_t k = 0;
+        pf_status st = launch(k++);
         int reps = trials;
         float ms = 0;
         for (int pass = 0; pass < 2 && st == PF_OK; ++pass) {
             (void)hipEventRecord(a, m->stream);
-            for (int t = 0; t < reps && st == PF_OK; ++t) st = launch();
+            for (int t = 0; t < reps && st == PF_OK; ++t) st = launch(k++);
             (void)hipEventRecord(b, m->stream);
             (void)hipEventSynchronize(b);
             (void)hipEventElapsedTime(&ms, a, b);
@@ -1254,8 +1279,12 @@ pf_status autotune(Model *m, int32_t trials)
             if (st != PF_OK || m->family != 0 || m->tb != tb || m->passes != passes) break;
             // reductions as pf_step takes them: partials, finalised many steps at a time
             float ms = 0;
-            st = time_steps([&] { return launch_step(m, m->parity, red, nullptr, false, tb, red ? m->part : nullptr); },
-                            tb, &ms);
+            st = time_steps(
+                [&](int64_t k) {
+                    m->fp32 ? point(m->a32, k) : point(m->a64, k);
+                    return launch_step(m, 0, red, nullptr, false, tb, red ? m->part : nullptr);
+                },
+                tb, &ms);
             if (st != PF_OK) break;
             if (ms < best) {
                 best = ms;
@@ -1281,7 +1310,6 @@ pf_status autotune(Model *m, int32_t trials)
         }
         auto set = [&](auto &to, const auto &from) {
             to = from;
-            to.parity = m->parity;
             if (red) {
                 to.part = part;
                 to.pstride = slots;
@@ -1294,7 +1322,8 @@ pf_status autotune(Model *m, int32_t trials)
         if (!red || part) {
             float ms = 0;
             st = time_steps(
-                [&] {
+                [&](int64_t k) {
+                    m->fp32 ? point(u.d32, k) : point(u.d64, k);
                     const hipError_t e = launch_deep(m, &u, dp, dp.steps, red);
                     return e == hipSuccess ? PF_OK : hip_fail(e, "deep-tile step launch");
                 },
@@ -1305,6 +1334,10 @@ pf_status autotune(Model *m, int32_t trials)
             (void)hipStreamSynchronize(m->stream);
             (void)hipFree(part);
         }
+    }
+    if (third) {
+        (void)hipStreamSynchronize(m->stream);
+        (void)hipFree(third);
     }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
