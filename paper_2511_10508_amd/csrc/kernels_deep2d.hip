@@ -118,10 +118,21 @@ bool plan_deep2d(const Launch &L, int64_t nx, int64_t ny, int64_t steps, bool re
 //   Model C 6000^2 (1.03-1.1) to 12000^2 (0.8)
 //   reductions, r = 1: Gray-Scott FP64 never (1.26), the others at 3000^2 (0.9-1.2;
 //   1500^2 2.0-2.9);  r = 2: 1500^2 (1.0-2.0) to 3000^2 (0.8-1.0)
-int64_t deep2d_most_sites(const Launch &L, bool red)
+// A call of one step has no second step to share a tile's loads: marching / deep
+// times of such calls were 0.88-0.92 for two fields in FP64 with reductions at 1024^2
+// to 3000^2 (1.15 at 515 x 389); 0.91 for Allen-Cahn r = 2 and Cahn-Hilliard r = 1 in
+// FP32 and Cahn-Hilliard r = 2 in FP64 at 1700^2 (1.2-1.4 at 1024^2); 0.91 for two
+// fields in FP32 with r = 2 at 6000^2 (1.03 at 3000^2); 0.98 or more elsewhere.
+int64_t deep2d_most_sites(const Launch &L, bool red, int64_t steps)
 {
     constexpr int64_t M = 1000000, all = INT64_MAX;
     const bool two = L.kind == kGS || L.kind == kMC;
+    if (steps == 1) {
+        if (red && two && !L.fp32) return M / 2;
+        if (!red && two && L.fp32 && L.r == 2) return 9 * M;
+        if (!red && (L.fp32 ? (L.kind == kAC && L.r == 2) || (L.kind == kCH && L.r == 1) : L.kind == kCH && L.r == 2))
+            return 3 * M / 2;
+    }
     if (!red) {
         if (L.r == 1) return all;
         if (L.kind == kAC) return L.fp32 ? 6 * M : all;

@@ -182,8 +182,9 @@ bool plan_deep3d(const Launch &L, int64_t nx, int64_t ny, int64_t nz, int64_t st
 // (steps per launch among them), and the microseconds of the whole chip that a step
 // takes.  false where the family does not cover L.
 bool plan_deep_served(const Launch &L, int64_t nx, int64_t ny, int64_t nz, Deep3Args *a, int32_t *tiles, double *work_us);
-// Sites up to which deep tiles are faster than the marching kernels.
-int64_t deep2d_most_sites(const Launch &L, bool red);
+// Sites up to which deep tiles are faster than the marching kernels (2D: in a call
+// of `steps` steps).
+int64_t deep2d_most_sites(const Launch &L, bool red, int64_t steps);
 int64_t deep3d_most_sites(const Launch &L, bool red);
 // Takes `steps` (at most plan.steps) steps from buf[parity] to buf[parity ^ 1]; with
 // red, step s leaves its partials in part[s kNumQ pstride ..] (pstride =

@@ -650,7 +650,8 @@ static bool deep_plan(const Model *m, int64_t nsteps, bool red, DeepPlan *plan)
     if (m->family != 0 || d.ndim < 2 || nsteps < 1) return false;
     const int64_t N = d.n[0] * d.n[1] * d.n[2];
     if (m->pinned() && (red || d.kind != PF_AC || d.ndim != 2 || N > 128 * 128)) return false;
-    if ((red || m->tuned != Model::kTunedDeep) && N > (d.ndim == 2 ? deep2d_most_sites(m->L, red) : deep3d_most_sites(m->L, red))) return false;
+    const int64_t most = d.ndim == 2 ? deep2d_most_sites(m->L, red, nsteps) : deep3d_most_sites(m->L, red);
+    if (N > most && (red || m->tuned != Model::kTunedDeep || nsteps == 1)) return false;
     return d.ndim == 2 ? plan_deep2d(m->L, d.n[0], d.n[1], nsteps, red, plan)
                        : plan_deep3d(m->L, d.n[0], d.n[1], d.n[2], nsteps, red, plan);
 }

@@ -96,3 +96,19 @@ def test_autotuner_times_steps_that_alternate_buffers(kind, n, order, prec):
     for f, a in enumerate(before):
         assert np.array_equal(m.get_field(f), a)
     assert m.tile()[0] == 0 and _deep(m)
+
+
+def test_a_call_of_one_step_marches_where_that_is_faster():
+    """Two FP64 fields with reductions, 1024^2: the sums of a call of one step have the
+    partition of the marching kernels, bitwise, those of a call of two have not."""
+    n, red = (1024, 1000), P.PF_REDUCE_EACH_STEP
+    a, b = _model(P.PF_GS, n, 2, P.PF_FP64, red), _model(P.PF_GS, n, 2, P.PF_FP64, red)
+    b.set_time_block(1)
+    same = {}
+    for steps in (1, 2):
+        for m in (a, b):
+            m.step(steps)
+        same[steps] = all(np.array_equal(x, y) for q in (P.PF_RED_MASS0, P.PF_RED_MASS1)
+                          for x, y in zip(a.reduce_history(q, steps), b.reduce_history(q, steps)))
+    assert same == {1: True, 2: False}
+    assert np.array_equal(a.get_field(0), b.get_field(0)) and np.array_equal(a.get_field(1), b.get_field(1))
