@@ -115,11 +115,12 @@ enum { PF_RED_MASS0 = 0, PF_RED_MASS1 = 1, PF_RED_ENERGY = 2, PF_RED_NONFINITE =
  *             1/c1 (AC) or 2/c1^2 (CH), the limit of the step linearised
  *             about the separated states c^2 = c1/c2 (+inf for c1 = 0).  The
  *             mass reductions apply, the free energy is PF_ERR_UNSUPPORTED.
- *             The model holds two half spectra besides its fields (hipFFT
- *             plans, used where an extent is no power of two the library's own
- *             transforms take, allocate their own work space) and keeps the updated
- *             spectrum between steps, so a run of steps takes two transforms
- *             per step; after pf_init, pf_set_field or pf_field_device the
+ *             The model holds two half spectra besides its fields and keeps
+ *             the updated spectrum between steps, so a run of steps takes two
+ *             transforms per step.  Grids of two or three axes whose extents are
+ *             powers of two (x 64 to 8192, the others 32 to 4096) run the
+ *             library's own transforms, others hipFFT plans, which allocate
+ *             their own work space.  After pf_init, pf_set_field or pf_field_device the
  *             next step transforms the state again.  Not accepted by the server.
  */
 typedef struct pf_desc {
@@ -181,7 +182,12 @@ pf_status pf_stability(const pf_desc *desc, double *dt_max);
  * per-site kernels where the fused ones do not apply: one for Cahn-Hilliard
  * and Model H, ndim for the direct biharmonic).  A 3D Cahn-Hilliard model
  * switched to two passes (pf_set_passes, or the autotuner's choice) holds
- * one field more.  0 for an invalid descriptor. */
+ * one field more.  With PF_REDUCE_EACH_STEP the partials of many steps are
+ * included (up to 1024 steps' within 32 MiB, and at least one launch's; a tile
+ * other than the library's may take other shares of that), the history of
+ * pf_reduce_history is not.  With PF_SPECTRAL the half spectra and twiddle
+ * tables are, the work areas of hipFFT plans are not.  0 for an invalid
+ * descriptor. */
 uint64_t pf_footprint_bytes(const pf_desc *desc);
 
 /* Elements of one device field buffer (pitch * n1 * n2).  -1 if invalid. */

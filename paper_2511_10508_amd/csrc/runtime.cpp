@@ -542,29 +542,62 @@ static void destroy_graphs(Model *m)
     m->graphs_valid = false;
 }
 
-constexpr int64_t kDeepPartPairs = 1 << 21;  // partials kept before they are finalised (32 MiB)
+static bool deep_plan(const Model *m, int64_t nsteps, bool red, DeepPlan *plan);
 
-// Partials of the steps since the last finalising launch, which takes as many
-// steps at once as 32 MiB hold (two launches of 9 us a step otherwise: as long as
-// a step of a 1024^2 grid).
+// Partials kept before they are finalised: as many steps' as 32 MiB hold, 1024 at
+// most, and never less than one launch's.
+constexpr int64_t kRedPairs = 1 << 21;
+constexpr int64_t kRedSteps = 1024;
+
+// Steps that a batch of launches of tb steps holds, `slots` partials a step and
+// `unit` steps at once, and the pairs of memory it takes.
+static int64_t red_keep(int64_t slots, int tb, int64_t unit)
+{
+    const int64_t keep = std::max<int64_t>(unit, std::min<int64_t>(kRedSteps, kRedPairs / (kNumQ * slots)));
+    return (keep + tb - 1) / tb * tb;
+}
+static int64_t red_pairs(int64_t slots, int tb, int64_t unit)
+{
+    const int64_t keep = red_keep(slots, tb, unit);
+    return keep * kNumQ * slots + finalize_scratch(slots, keep);
+}
+
+// Pairs that any pf_step call of a reducing model takes as it is planned now: the
+// deep plan, and with it the slots, depends on the steps of the call.
+static int64_t red_capacity(const Model *m)
+{
+    if (m->family != 0) return 0;
+    int64_t need = 0;
+    bool marches = false;
+    for (int64_t n : {1, 2, 3, 4, 6, 8, 12, 16, (int)kDeepMaxSteps}) {  // the plans' steps per launch
+        DeepPlan dp;
+        if (deep_plan(m, n, true, &dp))
+            need = std::max(need, red_pairs(dp.slots(), 1, dp.steps));
+        else
+            marches = true;
+    }
+    if (marches)
+        for (int tb : {1, m->tb}) need = std::max(need, red_pairs(m->fused_slots, tb, tb));
+    return need;
+}
+
+// Partials of the steps since the last finalising launch, which takes many steps at
+// once (two launches of 9 us a step otherwise: as long as a step of a 1024^2 grid).
 struct RedBatch {
     Model *m = nullptr;
     int64_t slots = 0, keep = 0, held = 0;
     int tb = 1;              // steps per launch in the partials' layout
     double2 *out = nullptr;  // results of the first step held
 
-    // room for `unit` steps per launch at least, in whole launches, and for 1024
-    // steps (as the history has), so that a later, longer call finds it in place
-    pf_status begin(Model *model, int64_t slots_, int tb_, int64_t unit, int64_t nsteps, double2 *out_)
+    // PF_ERR_NOMEM: no memory for one launch's partials; another path may do with less
+    pf_status begin(Model *model, int64_t slots_, int tb_, int64_t unit, double2 *out_)
     {
         m = model;
         slots = slots_;
         tb = tb_;
         out = out_;
-        const int64_t per_step = kNumQ * slots;
-        keep = std::max<int64_t>(unit, std::min<int64_t>(std::min<int64_t>(std::max<int64_t>(nsteps, 1024), 4096), kDeepPartPairs / per_step));
-        keep = (keep + tb - 1) / tb * tb;
-        const int64_t need = keep * per_step + finalize_scratch(slots, keep);
+        keep = red_keep(slots, tb, unit);
+        const int64_t need = red_pairs(slots, tb, unit);
         if (need <= m->deep_part_cap) return PF_OK;
         if (m->deep_part) {
             PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
@@ -573,9 +606,15 @@ struct RedBatch {
             m->deep_part_cap = 0;
             m->graphs_valid = false;  // captured launches hold the old address
         }
-        PF_HIP(hipMalloc((void **)&m->deep_part, sizeof(double2) * need), "hipMalloc(partials)");
-        m->deep_part_cap = need;
-        return PF_OK;
+        for (const int64_t pairs : {std::max(need, red_capacity(m)), need}) {
+            if (hipMalloc((void **)&m->deep_part, sizeof(double2) * pairs) == hipSuccess) {
+                m->deep_part_cap = pairs;
+                return PF_OK;
+            }
+            (void)hipGetLastError();
+            m->deep_part = nullptr;
+        }
+        return fail(PF_ERR_NOMEM, "no device memory for the reduction partials");
     }
     // where the next k steps leave their partials
     pf_status take(int64_t k, double2 **part)
@@ -607,9 +646,13 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
     g.par = par;
     g.steps = k;
     g.red = red;
-    const bool batch = red && m->family == 0;
+    bool batch = red && m->family == 0;
     RedBatch rb;
-    pf_status st = batch ? rb.begin(m, m->fused_slots, m->tb, m->tb, k, m->stage) : PF_OK;
+    pf_status st = batch ? rb.begin(m, m->fused_slots, m->tb, m->tb, m->stage) : PF_OK;
+    if (st == PF_ERR_NOMEM) {  // each step finalised by itself
+        batch = false;
+        st = PF_OK;
+    }
     if (st != PF_OK) return st;
     PF_HIP(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
     int p = par;
@@ -662,17 +705,14 @@ static hipError_t launch_deep(const Model *m, const void *args, const DeepPlan &
                              : launch_deep3d(m->L, args, plan, steps, red, m->stream);
 }
 
-// Runs nsteps steps on deep tiles, red: the reductions of every step into hist.
-static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, bool red, double2 *hist, bool timed)
+// Runs nsteps steps on deep tiles; rb (begun by the caller) takes the reductions of
+// every step.
+static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, RedBatch *rb, bool timed)
 {
     const int64_t slots = plan.slots();
+    const bool red = rb != nullptr;
     // as many launches as the plan's steps per launch need, the steps shared out evenly
     const int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
-    RedBatch rb;
-    if (red) {
-        pf_status st = rb.begin(m, slots, 1, plan.steps, nsteps, hist);
-        if (st != PF_OK) return st;
-    }
     union {
         StepArgs<double> d64;
         StepArgs<float> d32;
@@ -686,7 +726,7 @@ static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, bool
         const int64_t k = (nsteps - done + launches - i - 1) / (launches - i);
         double2 *part = nullptr;
         if (red) {
-            pf_status st = rb.take(k, &part);
+            pf_status st = rb->take(k, &part);
             if (st != PF_OK) return st;
         }
         auto set = [&](auto &a) {
@@ -715,7 +755,7 @@ static pf_status deep_steps(Model *m, const DeepPlan &plan, int64_t nsteps, bool
         m->steps_done += k;
         done += k;
     }
-    return red ? rb.flush() : PF_OK;
+    return red ? rb->flush() : PF_OK;
 }
 
 pf_status do_steps(Model *m, int64_t nsteps)
@@ -731,7 +771,13 @@ pf_status do_steps(Model *m, int64_t nsteps)
     const bool use_graph = (m->desc.flags & PF_USE_GRAPH) != 0 && !m->timing;
     int64_t done = 0;
     DeepPlan dp;
-    if (deep_plan(m, nsteps, each, &dp)) return deep_steps(m, dp, nsteps, each, m->hist, m->timing);
+    if (deep_plan(m, nsteps, each, &dp)) {
+        RedBatch rb;
+        const pf_status st = each ? rb.begin(m, dp.slots(), 1, dp.steps, m->hist) : PF_OK;
+        if (st == PF_OK) return deep_steps(m, dp, nsteps, each ? &rb : nullptr, m->timing);
+        if (st != PF_ERR_NOMEM) return st;
+        // the marching kernels leave far fewer partials
+    }
     if (use_graph && nsteps >= 2 * kGraphSteps) {
         if (!m->stage) PF_HIP(hipMalloc((void **)&m->stage, sizeof(double2) * kNumQ * kGraphSteps),
                               "hipMalloc(stage)");
@@ -763,14 +809,17 @@ pf_status do_steps(Model *m, int64_t nsteps)
     }
     // launches of m->tb steps, then an odd step by itself; the fused family's
     // reductions are finalised many steps at a time
-    const bool batch = each && m->family == 0;
     for (int tb : {m->tb, 1}) {
         const int64_t n = (nsteps - done) / tb * tb;
         if (n == 0) continue;
         RedBatch rb;
+        bool batch = each && m->family == 0;
         if (batch) {
-            pf_status st = rb.begin(m, m->fused_slots, tb, tb, n, m->hist + kNumQ * done);
-            if (st != PF_OK) return st;
+            pf_status st = rb.begin(m, m->fused_slots, tb, tb, m->hist + kNumQ * done);
+            if (st == PF_ERR_NOMEM)
+                batch = false;  // each step finalised by itself
+            else if (st != PF_OK)
+                return st;
         }
         for (int64_t i = 0; i < n; i += tb) {
             double2 *part = nullptr;
@@ -1466,6 +1515,17 @@ PF_API uint64_t pf_footprint_bytes(const pf_desc *desc)
     // reduction partials (per-wave pairs) and the result block
     bytes += sizeof(double2) * kNumQ * (uint64_t)std::max<int64_t>(reduce_partial_slots((int64_t)N), N / 64 + 1);
     bytes += sizeof(double2) * kNumQ;
+    if (desc->flags & PF_REDUCE_EACH_STEP) {
+        Model m;
+        m.desc = *desc;
+        m.nf = desc->nfields;
+        m.fp32 = desc->precision == PF_FP32;
+        m.L = Launch{(desc->kind == kCH && (desc->flags & PF_BIHARMONIC_DIRECT)) ? kCHD : desc->kind, desc->ndim,
+                     desc->order / 2, m.fp32 ? 1 : 0};
+        m.clen = default_chunk(desc);
+        plan(&m);
+        bytes += sizeof(double2) * (uint64_t)red_capacity(&m);
+    }
     return bytes;
 }
 

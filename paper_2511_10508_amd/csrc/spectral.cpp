@@ -66,8 +66,13 @@ void spectral_release(Model *m)
 // Bytes of the two half spectra of a descriptor.
 uint64_t spectral_bytes(const pf_desc *d)
 {
-    const uint64_t cb = d->precision == PF_FP32 ? 8 : 16;
-    return 2ull * (uint64_t)(d->n[0] / 2 + 1) * (uint64_t)d->n[1] * (uint64_t)d->n[2] * cb;
+    const bool fp32 = d->precision == PF_FP32;
+    const bool own = own_fft_available(Launch{d->kind, d->ndim, d->order / 2, fp32}, d->n[0], d->n[1], d->n[2]);
+    const int64_t width = own ? fft_columns(fp32, d->n[0]) : d->n[0] / 2 + 1;
+    uint64_t bytes = 2ull * (uint64_t)width * (uint64_t)d->n[1] * (uint64_t)d->n[2] * (fp32 ? 8 : 16);
+    if (own)  // twiddle tables
+        for (int a = 0; a < d->ndim; ++a) bytes += 16ull * (uint64_t)d->n[a];
+    return bytes;
 }
 
 // exp(-2 pi i k / n), k < n, rounded once from long double to FP64, on the device.
