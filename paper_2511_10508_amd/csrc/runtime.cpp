@@ -35,6 +35,7 @@ pf_status fail(pf_status s, const std::string &msg)
 pf_status hip_fail(hipError_t e, const char *what)
 {
     g_err = std::string(what) + ": " + hipGetErrorString(e);
+    (void)hipGetLastError();  // reported here: the next launch's check would take it for its own
     return PF_ERR_DEVICE;
 }
 
@@ -525,6 +526,7 @@ static pf_status ensure_history(Model *m, int64_t n)
         PF_HIP(hipStreamSynchronize(m->stream), "hipStreamSynchronize");
         PF_HIP(hipFree(m->hist), "hipFree(history)");
         m->hist = nullptr;
+        m->hist_cap = m->hist_len = 0;
     }
     const int64_t cap = std::max<int64_t>(n, 1024);
     PF_HIP(hipMalloc((void **)&m->hist, sizeof(double2) * kNumQ * cap), "hipMalloc(history)");

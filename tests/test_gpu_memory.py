@@ -40,3 +40,15 @@ def test_memory_of_a_reducing_model(kind, n, order, prec):
     for steps in (1000, 2, 3, 7, 25, 1):
         m.step(steps)
         assert before - _free() == held, steps
+
+
+def test_a_history_too_long_for_memory_leaves_a_usable_model():
+    m = _model(P.PF_CH, (70, 50), 2, P.PF_FP64)
+    m.step(3)
+    with pytest.raises(P.PfError):
+        m.step(10 ** 10)  # 480 GB of history: refused before anything is launched
+    assert m.steps_done() == 3
+    m.step(5)
+    assert m.steps_done() == 8
+    hi, _ = m.reduce_history(P.PF_RED_MASS0, 5)
+    assert abs(hi[4] - m.reduce(P.PF_RED_MASS0)[0]) <= 1e-12 * 70 * 50
