@@ -61,7 +61,7 @@ struct Req {
     int64_t finish_tick = -1;
     int cls = -1;            // batched class, -1 = stepped on its own
     int dcls = -1;           // batched class on deep tiles, -1 = none
-    double march_us = 20.0;  // a step on its marching tiles alone (from the autotuner)
+    double march_us = 0.0;   // a step on its marching tiles alone (tune_served)
     double2 *pinned = nullptr;  // final reductions (slot of the server's pinned pool)
     int slot = -1;
     pf_result res{};
@@ -133,7 +133,8 @@ struct Server {
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t fork = nullptr;
     hipEvent_t tev[2] = {nullptr, nullptr};  // autotuner timing
-    // serving autotuner: chunk and microseconds per step, per (class, log2 of each extent)
+    // serving autotuner: chunk, and microseconds of a step per march_work(), per (class,
+    // log2 of each extent); 0: not measured
     std::map<std::tuple<int, int, int, int>, std::pair<int32_t, double>> tuned;
     // written by the scheduler thread, read by pf_server_stats from any thread
     std::atomic<int64_t> tick{0}, launches{0}, captures{0}, replays{0};
@@ -344,6 +345,18 @@ static hipError_t upload_table(Server *s, const ClassTables &t, const void *host
     return e;
 }
 
+// The share of the chip that a model's marching tiles fill (3D: workgroups, 2D: four
+// waves each).
+static double march_part(const Model *m) { return m->items / (m->desc.ndim == 3 ? 150.0 : 1440.0); }
+
+// What a marching step's time is proportional to within a bucket: rounds of work
+// items over the chip, times the rows or planes of an item.
+static double march_work(const Model *m)
+{
+    const int64_t march = m->desc.ndim == 2 ? m->desc.n[1] : m->desc.n[2];
+    return std::max(1.0, march_part(m)) * (double)std::min<int64_t>(m->clen, march);
+}
+
 // Serving autotuner.  The chunk length (rows or planes marched per work item)
 // of each kernel class and size bucket (log2 of every extent) is chosen on
 // the first request of the bucket: for every candidate chunk the class's
@@ -358,7 +371,12 @@ static hipError_t upload_table(Server *s, const ClassTables &t, const void *host
 static void tune_served(Server *s, Req *r)
 {
     Model *m = r->m;
-    if (r->cls < 0 || !s->tune) return;
+    if (r->cls < 0) return;
+    // not measured: the latency of a small step, or the fields' bytes (six requests, us per
+    // step: 3000^2 Allen-Cahn p4 FP64 161, 864 MB; 200^3 Gray-Scott p2 FP32 264, 768 MB)
+    const double bytes = 2.0 * (double)m->nf * (double)m->elems * (m->fp32 ? 4 : 8);
+    r->march_us = std::max(20.0, bytes / (m->desc.ndim == 2 ? 6e6 : 3.5e6));
+    if (!s->tune) return;
     ClassTables &t = s->classes[r->cls];
     if (t.tiny) return;
     const pf_desc &d = m->desc;
@@ -367,7 +385,7 @@ static void tune_served(Server *s, Req *r)
     auto it = s->tuned.find(key);
     if (it != s->tuned.end()) {
         if (it->second.first != m->clen) set_chunk(m, it->second.first);
-        r->march_us = it->second.second;
+        if (it->second.second > 0.0) r->march_us = it->second.second * march_work(m);
         return;
     }
     const int32_t keep = m->clen;
@@ -376,7 +394,7 @@ static void tune_served(Server *s, Req *r)
         const size_t total = t.args_bytes + sizeof(int32_t) * (2 * s->max_slots + 2);
         if (hipMalloc(&t.tune_dev, total) != hipSuccess ||
             hipHostMalloc(&t.tune_host, total, hipHostMallocDefault) != hipSuccess) {
-            s->tuned[key] = {keep, r->march_us};
+            s->tuned[key] = {keep, 0.0};
             return;
         }
     }
@@ -412,7 +430,7 @@ static void tune_served(Server *s, Req *r)
     }
     if (set_chunk(m, best) != PF_OK) (void)set_chunk(m, keep);
     if (best_t < 1e300) r->march_us = best_t * (double)sites * 1e3 / 3;  // of three launches
-    s->tuned[key] = {m->clen, r->march_us};
+    s->tuned[key] = {m->clen, best_t < 1e300 ? r->march_us / march_work(m) : 0.0};
 }
 
 // The graph of S chained batched launches of class c for table buffer `set`
@@ -504,7 +522,7 @@ static std::vector<char> deep_classes(Server *s, const std::vector<Req *> &run)
     for (const Req *r : run) {
         if (r->cls < 0 || r->dcls < 0) continue;
         Load &l = load[r->cls];
-        const double part = r->m->items / (r->desc.ndim == 3 ? 150.0 : 1440.0);  // of the chip
+        const double part = march_part(r->m);
         // chained steps alone take about half as long again as the autotuner's launches
         l.slowest = std::max(l.slowest, 1.5 * r->march_us);
         l.sum += 1.2 * r->march_us * std::min(1.0, part);
