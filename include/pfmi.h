@@ -459,14 +459,18 @@ typedef struct pf_result {
  * two steps per launch where their class has a two-step kernel (2D orders 2
  * and 4, 3D order 2), and the chunk length the server's autotuner picks per
  * kernel class and size bucket on the first request of each bucket.
+ * Classes with register tiles (orders 2 and 4) run on those, up to 8 steps per
+ * launch in 2D and 2 in 3D, in the ticks where an estimate from the measured
+ * chunk times finds that faster.
  * Requests whose grid fits one workgroup's LDS (2D or 3D Allen-Cahn,
  * Cahn-Hilliard, Gray-Scott or Model C, order <= 8, x extent <= 1024, both
  * copies of the fields plus mu or g within 128 KiB) form a tiny class: one
  * workgroup per request keeps the whole grid in LDS and runs up to
  * 16 x steps_per_tick of its steps per tick, touching HBM once per tick.
  * Environment: PFMI_SERVER_MAX_GRAPHS bounds the cache of captured tick
- * graphs (default 256); PFMI_SERVER_TWO_STEP=0 keeps one step per launch;
- * PFMI_SERVER_TUNE=off keeps the library's default chunk.
+ * graphs (default 256); PFMI_SERVER_TWO_STEP=0 keeps one step per launch,
+ * on marching tiles; PFMI_SERVER_TUNE=off keeps the library's default chunk of
+ * these and estimates without measuring.
  */
 pf_status pf_server_create(int32_t device, uint64_t hbm_budget, int32_t max_slots,
                            int32_t steps_per_tick, pf_server **out);

@@ -106,8 +106,8 @@ struct Server {
     int max_slots = 0;
     int spt = 64;
     int max_graphs = kMaxGraphs;
-    bool two_step = true;  // two-step batched kernels where the class has them (PFMI_SERVER_TWO_STEP)
-    bool tune = true;      // serving autotuner (PFMI_SERVER_TUNE=off disables it)
+    bool two_step = true;  // several steps per batched launch where the class can (PFMI_SERVER_TWO_STEP)
+    bool tune = true;      // serving autotuner of the marching tiles (PFMI_SERVER_TUNE=off disables it)
     hipStream_t stream = nullptr, copy_stream = nullptr;
     std::chrono::steady_clock::time_point t0;
 
@@ -697,7 +697,8 @@ static void worker_main(Server *s)
                 (void)set_chunk(m, m->clen);
             }
             r->cls = class_of(s, m);
-            if (r->cls >= 0) r->dcls = class_of(s, m, true);
+            // without two-step launches no request takes several steps per launch
+            if (r->cls >= 0 && s->two_step) r->dcls = class_of(s, m, true);
             r->state = RUNNING;
             s->active.push_back(r);  // a cancel during admission takes effect at the next tick
         }
