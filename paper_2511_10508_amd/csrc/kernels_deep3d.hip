@@ -20,8 +20,8 @@ constexpr double kOps[4][2][2][2][2] = {
     // [kind][r - 1][fp64][red][tall]
     {{{{4, 4}, {31, 42}}, {{4, 10}, {39, 53}}}, {{{7, 9}, {61, 68}}, {{6, 17}, {69, 157}}}},        // AC
     {{{{12, 20}, {54, 120}}, {{20, 41}, {65, 100}}}, {{{60, 60}, {110, 110}}, {{70, 70}, {300, 300}}}},  // CH
-    {{{{14, 22}, {49, 63}}, {{24, 43}, {73, 210}}}, {{{17, 45}, {85, 133}}, {{29, 68}, {400, 600}}}},   // GS
-    {{{{15, 32}, {48, 64}}, {{26, 61}, {90, 248}}}, {{{17, 50}, {89, 146}}, {{36, 121}, {400, 600}}}},  // MC
+    {{{{14, 22}, {49, 63}}, {{24, 43}, {73, 73}}}, {{{17, 45}, {85, 133}}, {{29, 68}, {400, 400}}}},   // GS
+    {{{{15, 32}, {48, 64}}, {{26, 61}, {90, 90}}}, {{{17, 50}, {89, 146}}, {{36, 121}, {400, 400}}}},  // MC
 };
 
 }  // namespace

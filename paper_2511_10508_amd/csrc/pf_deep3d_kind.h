@@ -25,8 +25,12 @@ using Deep3Flat = Deep3Tile<2, 8, (sizeof(T) == 4 && !RED) ? 4 : 2>;
 // Twelve planes: more steps per launch for r = 1, and the least that a
 // Cahn-Hilliard step with r = 2 (halo 4) can do with; sixteen for FP32 there
 // (96^3 12.5 against 16.5 us).
+// FP64 two-field kernels with reductions stay flat (a tall Model C brick spills
+// 880 B a lane, and no grid below the size limit planned one).
 template <typename T, int KIND, int R, bool RED>
-using Deep3Tall = Deep3Tile<2, (KIND == kCH && R == 2 && sizeof(T) == 4 && !RED) ? 16 : 12, 2>;
+using Deep3Tall =
+    std::conditional_t<sizeof(T) == 8 && RED && (KIND == kGS || KIND == kMC), Deep3Flat<T, KIND, R, RED>,
+                       Deep3Tile<2, (KIND == kCH && R == 2 && sizeof(T) == 4 && !RED) ? 16 : 12, 2>>;
 // FP64 two-field kernels with r = 2 and reductions spill a kilobyte a lane
 // (96^3 66 us a step against 30 us marching): not built.
 template <typename T, int KIND, int R, bool RED>
