@@ -64,7 +64,7 @@ bool plan_deep2d(const Launch &L, int64_t nx, int64_t ny, int64_t steps, bool re
                             if (TX - 2 * hx < 8 || TY - 2 * hy < 4) continue;
                             const int64_t tx = cdiv(nx, TX - 2 * hx), ty = cdiv(ny, TY - 2 * hy);
                             const int64_t tiles = tx * ty;
-                            if (tiles * waves > (1 << 30)) continue;
+                            if (tiles * waves >= kDeepMaxWaves) continue;
                             const double b = (double)tiles / kCUs;
                             auto step_us = [&](double blocks) {
                                 return blocks * waves / 4 * wave_ops * 4 / 2400.0 +

@@ -62,7 +62,7 @@ bool plan_deep3d(const Launch &L, int64_t nx, int64_t ny, int64_t nz, int64_t st
                             if (TX - 2 * hx < 4 || TY - 2 * hy < 2) continue;
                             const int64_t tx = cdiv(nx, TX - 2 * hx), ty = cdiv(ny, TY - 2 * hy);
                             const int64_t tzs = cdiv(nz, LZ - 2 * h), tiles = tx * ty * tzs;
-                            if (tiles * waves > (1 << 30)) continue;
+                            if (tiles * waves >= kDeepMaxWaves) continue;
                             const double b = (double)tiles / kCUs;
                             auto step_us = [&](double blocks) {
                                 return blocks * waves / 4 * wave_ops * 4 / 2400.0 + (blocks <= 1 ? 0.48 * stages : 0.0);

@@ -156,6 +156,7 @@ hipError_t launch_tiny(const Launch &L, const void *table, int32_t blocks, hipSt
 // steps per launch on tiles held in registers (pf_deep2d.h, pf_deep3d.h).
 constexpr int kDeepWaves = 16;      // most waves per workgroup
 constexpr int kDeepMaxSteps = 24;   // most steps per launch
+constexpr int64_t kDeepMaxWaves = 1 << 26;  // a launch holds fewer than 2^32 threads
 struct DeepArgs {
     int32_t steps;           // time steps of this launch
     int32_t hx, hy;          // halo columns and rows per side
