@@ -681,6 +681,30 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
     return PF_OK;
 }
 
+// Estimated microseconds of a step on the model's marching tiles (one step per launch):
+// a launch, the rows or planes of a work item one after the other, and the sites
+// computed, halo included; or the fields' bytes at 5.5 TB/s.  Fitted to 7400 models
+// of 400 shapes (half of them with an extent of 1 to 24): 10 % of the estimates are
+// below 0.6-0.9, 10 % above 1.1-1.25 of the measured time.
+static double march_step_us(const Model *m, bool red)
+{
+    const pf_desc &d = m->desc;
+    const bool f32 = m->fp32, two = m->nf == 2;
+    const int64_t march = d.ndim == 2 ? d.n[1] : d.n[2];
+    const double len = (double)(std::min<int64_t>(m->clen, march) + (d.kind == kCH ? 4 : 2) * m->L.r);
+    const double msites = 1e-6 * m->items * (d.ndim == 2 ? 64 : m->threads) * (f32 ? 4 : 2) * len;
+    double us;
+    if (d.ndim == 2) {
+        us = 3.0 + (red ? 0.5 : 0.0) + ((f32 ? 0.45 : 0.25) + (two ? 0.1 : 0.0) + (red ? 0.12 : 0.0)) * len +
+             (f32 ? 0.42 : 1.0) * (two ? 1.9 : 1.0) * (red ? 1.15 : 1.0) * msites;
+    } else {
+        const double edge = f32 && d.n[0] < 32 ? 1.5 : 1.0;  // every lane wraps its columns by itself
+        us = (f32 ? 7.0 : 5.0) + (red ? 1.5 : 0.0) + ((f32 ? 0.75 : 0.5) + (two ? 0.3 : 0.0) + (red ? 0.3 : 0.0)) * len +
+             ((f32 ? 0.4 : 0.75) * (two ? 1.7 : 1.0) + (red ? 0.4 : 0.0)) * edge * msites;
+    }
+    return std::max(us, 2.0 * (double)m->elems * m->nf * (f32 ? 4 : 8) / 5.5e6);
+}
+
 // Whether a call of nsteps steps runs on deep tiles, and its plan: up to the size
 // where the marching kernels overtake them (deep2d_most_sites), or, without
 // per-step reductions, where the autotuner measured them faster (with them the
@@ -697,8 +721,19 @@ static bool deep_plan(const Model *m, int64_t nsteps, bool red, DeepPlan *plan)
     if (m->pinned() && (red || d.kind != PF_AC || d.ndim != 2 || N > 128 * 128)) return false;
     const int64_t most = d.ndim == 2 ? deep2d_most_sites(m->L, red, nsteps) : deep3d_most_sites(m->L, red);
     if (N > most && (red || m->tuned != Model::kTunedDeep || nsteps == 1)) return false;
-    return d.ndim == 2 ? plan_deep2d(m->L, d.n[0], d.n[1], nsteps, red, plan)
-                       : plan_deep3d(m->L, d.n[0], d.n[1], d.n[2], nsteps, red, plan);
+    if (!(d.ndim == 2 ? plan_deep2d(m->L, d.n[0], d.n[1], nsteps, red, plan)
+                      : plan_deep3d(m->L, d.n[0], d.n[1], d.n[2], nsteps, red, plan)))
+        return false;
+    // The size limits are those of squares and cubes.  On a thin grid most of a tile is
+    // not written (2000000 x 1 Gray-Scott p2 FP32 46 us a step, 7 marching; 500 x 500 x
+    // 1 Cahn-Hilliard p4 FP64 27 and 11): there the estimates decide (the plans' are
+    // 0.9-1.35 of the measured time).  Of 3900 thin models 35 then took deep tiles at
+    // 1.05-1.3 times the marching time, 100 marched at 1.05-1.7 times the deep one.
+    const bool thin = d.ndim == 2 ? d.n[1] < 16 : std::min({d.n[0], d.n[1], d.n[2]}) < 64;
+    if (thin && (red || m->tuned != Model::kTunedDeep || nsteps == 1) &&
+        1.06 * plan->us > (d.ndim == 2 ? 0.95 : 1.0) * march_step_us(m, red))
+        return false;
+    return true;
 }
 
 static hipError_t launch_deep(const Model *m, const void *args, const DeepPlan &plan, int32_t steps, bool red)

@@ -112,3 +112,14 @@ def test_a_call_of_one_step_marches_where_that_is_faster():
                           for x, y in zip(a.reduce_history(q, steps), b.reduce_history(q, steps)))
     assert same == {1: True, 2: False}
     assert np.array_equal(a.get_field(0), b.get_field(0)) and np.array_equal(a.get_field(1), b.get_field(1))
+
+
+def test_thin_grids_march_where_tiles_are_mostly_halo():
+    """Grids of a few rows or planes, wide enough to fill the chip: a tile computes tens
+    of rows to write them.  Small thin grids stay on deep tiles, where the launch counts."""
+    for kind, n, order, prec in ((P.PF_GS, (400000, 1), 2, P.PF_FP32), (P.PF_CH, (400000, 2), 4, P.PF_FP64),
+                                 (P.PF_MC, (2000000, 4), 4, P.PF_FP32), (P.PF_CH, (1, 500, 500), 4, P.PF_FP64)):
+        for flags in (0, P.PF_REDUCE_EACH_STEP):
+            assert not _deep(_model(kind, n, order, prec, flags)), (n, flags)
+    for kind, n in ((P.PF_GS, (5000, 1)), (P.PF_AC, (1, 5000)), (P.PF_GS, (60, 60, 1)), (P.PF_MC, (700, 500))):
+        assert _deep(_model(kind, n)), n
