@@ -655,6 +655,9 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
         batch = false;
         st = PF_OK;
     }
+    // the temporary of the per-site kernels: nothing may be allocated under capture
+    const bool one_pass = (mh2d_available(m->L) || mh3d_available(m->L)) && !(m->desc.flags & PF_FORCE_GENERIC);
+    if (st == PF_OK && m->family == 1 && !one_pass) st = ensure_scratch(m);
     if (st != PF_OK) return st;
     PF_HIP(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
     int p = par;
@@ -670,6 +673,7 @@ static pf_status capture_graph(Model *m, int par, int k, bool red, Model::Graph 
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamEndCapture(m->stream, &graph);
     if (st != PF_OK) {
+        (void)hipGetLastError();
         if (graph) (void)hipGraphDestroy(graph);
         return st;
     }

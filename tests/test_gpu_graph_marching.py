@@ -39,3 +39,25 @@ def test_graph_replay_of_marching_kernels_is_bitwise_eager(kind, ndim, shape, or
     a.timing(True)
     a.step(64)
     assert a.timing_read()[1] == 64
+
+
+@pytest.mark.parametrize("kind,ndim,shape,order", [(P.PF_CH, 2, (1, 40, 70), 10), (P.PF_CH, 3, (11, 20, 30), 8),
+                                                   (P.PF_MC, 2, (1, 40, 70), 12)])
+def test_graph_replay_of_per_site_kernels_is_bitwise_eager(kind, ndim, shape, order):
+    """Orders that run the per-site kernels, which hold a field-sized temporary: it is there
+    before the first capture."""
+    params = BASE[kind][0]
+    n = (shape[2], shape[1], shape[0])[:ndim]
+    dt = 0.5 * dt_for(kind, ndim, order, params)
+    f0 = fields_for(kind, shape, 23)
+    got = []
+    for flags in (0, P.PF_USE_GRAPH):
+        m = P.Model(P.make_desc(kind, n, dt=dt, order=order, params=params, flags=flags))
+        assert m.tile()[1] == 1
+        for f, a in enumerate(f0):
+            m.set_field(f, a)
+        for steps in (64, 5, 70):
+            m.step(steps)
+        got.append([m.get_field(f) for f in range(len(f0))])
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
