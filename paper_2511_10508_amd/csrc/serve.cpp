@@ -510,14 +510,14 @@ static hipError_t run_classes(Server *s, const std::vector<int> &cls, int set, i
 // 128^3 112 / 149; FP64 2D Allen-Cahn p4, six of 700^2 19 / 19, 3000^2 161 / 184.
 // The estimates are good to about 20 %, hence the 0.8; 2D with r = 1 was faster
 // on deep tiles at every size (300^2 to 3000^2, one and six requests, 1.3-2.9 times),
-// but for grids of a few rows, whose tiles are mostly halo.
+// unless most of the work is grids of a few rows, whose tiles are mostly halo.
 // 24 mixed FP32 requests (2D to 512^2, 3D to 96^3) take 33 ms, 75 ms on marching tiles
 // alone; 64 of them 55 and 101 ms.
 static std::vector<char> deep_classes(Server *s, const std::vector<Req *> &run)
 {
     struct Load {
         double slowest = 0.0, sum = 0.0, deep = 0.0;
-        bool wide = true;  // 2D, r = 1, and no grid of a few rows
+        double wide = 0.0, tiles = 0.0;  // deep tiles of 2D, r = 1 on more than a few rows; all
     };
     std::vector<Load> load(s->classes.size());
     std::vector<char> deep(s->classes.size(), 0);
@@ -530,8 +530,9 @@ static std::vector<char> deep_classes(Server *s, const std::vector<Req *> &run)
         l.sum += 1.2 * r->march_us * std::min(1.0, part);
         if (l.deep == 0.0) l.deep = 6.0 / s->classes[r->dcls].tb;
         l.deep += r->m->serve_us;
-        l.wide = l.wide && r->desc.ndim == 2 && r->m->L.r == 1 && r->desc.n[1] >= 16;
-        deep[r->cls] = l.wide || l.deep < 0.8 * std::max(l.slowest, l.sum);
+        l.tiles += r->m->serve_us;
+        if (r->desc.ndim == 2 && r->m->L.r == 1 && r->desc.n[1] >= 16) l.wide += r->m->serve_us;
+        deep[r->cls] = l.wide > 0.5 * l.tiles || l.deep < 0.8 * std::max(l.slowest, l.sum);
     }
     return deep;
 }
