@@ -252,13 +252,17 @@ pf_status pf_field_device(pf_model *m, int32_t field, void **ptr, int64_t *pitch
  * (asynchronous).  With PF_REDUCE_EACH_STEP the reductions of the state at
  * the start of every step are fused into the step kernel and kept in a
  * device history (pf_reduce_history).  With PF_USE_GRAPH the launches are
- * replayed from captured HIP graphs.  2D Allen-Cahn, Cahn-Hilliard,
- * Gray-Scott and Model C models of order 2 or 4 whose tile and time block the
- * caller has not set run up to 24 steps per launch on register tiles where
- * that is faster (by a rule on model, order, precision, reductions and size;
- * such launches are not captured: PF_USE_GRAPH makes no difference); the
- * fields are bitwise the same, the fused reductions agree to their
- * compensated accuracy.
+ * replayed from captured HIP graphs.  2D and 3D Allen-Cahn, Cahn-Hilliard,
+ * Gray-Scott and Model C models of order 2 or 4 whose tile, time block, 3D
+ * layout and passes the caller has not set run up to 24 (2D) or 4 (3D) steps
+ * per launch on register tiles where that is faster (by a rule on model, order,
+ * precision, reductions, shape and the steps of the call, or as pf_autotune
+ * found; such launches are not captured: PF_USE_GRAPH makes no difference); the
+ * fields are bitwise the same, the fused reductions agree to their compensated
+ * accuracy.  The first reducing call allocates the partials that
+ * pf_footprint_bytes counts (and a longer history than before is allocated by
+ * the call that asks for it); where the register tiles' find no memory the call
+ * marches.
  */
 pf_status pf_step(pf_model *m, int64_t nsteps);
 

@@ -44,7 +44,7 @@ struct Model {
     // autotuned to deep tiles: the getters report the library's choice, which set on
     // another model gives the same tiles
     bool on_deep() const { return tuned == kTunedDeep && !pinned(); }
-    double2 *deep_part = nullptr;  // reduction partials of several deep-tile launches
+    double2 *deep_part = nullptr;  // reduction partials of many steps (RedBatch)
     int64_t deep_part_cap = 0;
     int32_t clen = 0, strips = 0, ow = 0, ytiles = 1, chunks = 0, items = 0, blocks = 0,
             threads = 0;
