@@ -1335,7 +1335,58 @@ pf_status autotune(Model *m, int32_t trials)
         *out = ms / ((float)reps * per);
         return st;
     };
-    pf_status st = PF_OK;
+    // Deep tiles, first: where they are far ahead the marching candidates are not timed
+    // for long.  As a model with the library's choices plans them; not where their
+    // partials find no memory.
+    float deep_ms = 1e30f, best_march = 1e30f;
+    auto time_deep = [&] {
+        m->pin_tile = m->pin_tb = m->pin_rows = m->pin_passes = false;
+        m->tuned = Model::kTunedDeep;
+        m->tb = 1;
+        m->rpw_req = m->passes_req = 0;
+        pf_status st = set_chunk(m, 0);
+        DeepPlan dp;
+        if (st != PF_OK || !deep_plan(m, 1 << 20, red, &dp)) return st;
+        union {
+            StepArgs<double> d64;
+            StepArgs<float> d32;
+        } u;
+        double2 *part = nullptr;
+        const int64_t slots = dp.slots();
+        if (red && hipMalloc((void **)&part, sizeof(double2) * kNumQ * slots * dp.steps) != hipSuccess) {
+            (void)hipGetLastError();
+            return st;
+        }
+        auto set = [&](auto &to, const auto &from) {
+            to = from;
+            if (red) {
+                to.part = part;
+                to.pstride = slots;
+            }
+        };
+        if (m->fp32)
+            set(u.d32, m->a32);
+        else
+            set(u.d64, m->a64);
+        float ms = 0;
+        st = time_steps(
+            [&](int64_t k) {
+                m->fp32 ? point(u.d32, k) : point(u.d64, k);
+                const hipError_t e = launch_deep(m, &u, dp, dp.steps, red);
+                return e == hipSuccess ? PF_OK : hip_fail(e, "deep-tile step launch");
+            },
+            dp.steps, &ms);
+        if (part) {
+            (void)hipStreamSynchronize(m->stream);
+            (void)hipFree(part);
+        }
+        if (st == PF_OK) {
+            deep_ms = std::min(deep_ms, ms);
+            best = std::min(best, ms);
+        }
+        return st;
+    };
+    pf_status st = time_deep();
     // (tb, rpw, passes): every time block and 3D tile layout in one pass, and
     // the two-pass form where it exists
     std::vector<std::array<int, 3>> forms;
@@ -1344,6 +1395,7 @@ pf_status autotune(Model *m, int32_t trials)
             if (d.ndim != 3 ? rpw == 2 : rows_per_wave_available(m->L, tb, rpw)) forms.push_back({tb, rpw, 1});
     if (two_pass_available(m->L) && !(d.flags & PF_FORCE_GENERIC)) forms.push_back({1, 2, 2});
     for (const auto &fm : forms) {
+        if (st != PF_OK) break;
         const int tb = fm[0], rpw = fm[1], passes = fm[2];
         std::vector<int32_t> lens = cand;
         if (d.ndim == 3) {
@@ -1377,55 +1429,18 @@ pf_status autotune(Model *m, int32_t trials)
                 },
                 tb, &ms);
             if (st != PF_OK) break;
-            if (ms < best) {
-                best = ms;
+            best = std::min(best, ms);
+            if (ms < best_march) {
+                best_march = ms;
                 bestc = {c, tb, m->rpw_req, passes, false, N};
             }
         }
-        if (st != PF_OK) break;
     }
-    // deep tiles, the same way (not where their partials find no memory)
-    m->pin_tile = m->pin_tb = m->pin_rows = m->pin_passes = false;
-    m->tuned = Model::kTunedDeep;
-    DeepPlan dp;
-    if (st == PF_OK && deep_plan(m, 1 << 20, red, &dp)) {
-        union {
-            StepArgs<double> d64;
-            StepArgs<float> d32;
-        } u;
-        double2 *part = nullptr;
-        const int64_t slots = dp.slots();
-        if (red && hipMalloc((void **)&part, sizeof(double2) * kNumQ * slots * dp.steps) != hipSuccess) {
-            (void)hipGetLastError();
-            part = nullptr;
-        }
-        auto set = [&](auto &to, const auto &from) {
-            to = from;
-            if (red) {
-                to.part = part;
-                to.pstride = slots;
-            }
-        };
-        if (m->fp32)
-            set(u.d32, m->a32);
-        else
-            set(u.d64, m->a64);
-        if (!red || part) {
-            float ms = 0;
-            st = time_steps(
-                [&](int64_t k) {
-                    m->fp32 ? point(u.d32, k) : point(u.d64, k);
-                    const hipError_t e = launch_deep(m, &u, dp, dp.steps, red);
-                    return e == hipSuccess ? PF_OK : hip_fail(e, "deep-tile step launch");
-                },
-                dp.steps, &ms);
-            bestc.deep = st == PF_OK && ms < best;
-        }
-        if (part) {
-            (void)hipStreamSynchronize(m->stream);
-            (void)hipFree(part);
-        }
-    }
+    // launches after the first few run at the clocks of a busy chip: a close second is
+    // timed again
+    if (st == PF_OK && deep_ms < 1.2f * best_march && !(deep_ms < best_march)) st = time_deep();
+    bestc.deep = st == PF_OK && deep_ms < best_march;
+    if (bestc.deep && red) bestc = {0, 1, 0, 0, true, N};  // the library's choices, as the getters report
     if (third) {
         (void)hipStreamSynchronize(m->stream);
         (void)hipFree(third);

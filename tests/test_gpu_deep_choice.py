@@ -123,3 +123,20 @@ def test_thin_grids_march_where_tiles_are_mostly_halo():
             assert not _deep(_model(kind, n, order, prec, flags)), (n, flags)
     for kind, n in ((P.PF_GS, (5000, 1)), (P.PF_AC, (1, 5000)), (P.PF_GS, (60, 60, 1)), (P.PF_MC, (700, 500))):
         assert _deep(_model(kind, n)), n
+
+
+def test_tuned_deep_models_with_reductions_have_the_defaults_partition():
+    """A reducing model that the autotuner put on deep tiles, whatever tile it had before:
+    every call's sums are bitwise those of a model with the library's choices."""
+    n, red = (700, 500), P.PF_REDUCE_EACH_STEP
+    ref = _model(P.PF_GS, n, 2, P.PF_FP64, red)
+    m = _model(P.PF_GS, n, 2, P.PF_FP64, red)
+    m.set_tile(24)
+    m.autotune(2)
+    assert m.tile()[0] == 0
+    for steps in (1, 2, 9):
+        for x in (ref, m):
+            x.step(steps)
+        for q in (P.PF_RED_MASS0, P.PF_RED_MASS1):
+            for a, b in zip(ref.reduce_history(q, steps), m.reduce_history(q, steps)):
+                assert np.array_equal(a, b), steps
