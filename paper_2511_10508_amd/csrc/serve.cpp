@@ -173,9 +173,10 @@ static int class_of(Server *s, const Model *m, bool deep = false)
     const size_t argsz = m->fp32 ? sizeof(StepArgs<float>) : sizeof(StepArgs<double>);
     t.args_bytes = argsz * s->max_slots;
     const size_t total = t.args_bytes + sizeof(int32_t) * (2 * s->max_slots + 2);
-    for (int b = 0; b < 2; ++b) {
-        if (hipMalloc(&t.dev[b], total) != hipSuccess) return -1;
-        if (hipHostMalloc(&t.host[b], total, hipHostMallocDefault) != hipSuccess) return -1;
+    hipError_t e = hipSuccess;
+    for (int b = 0; b < 2 && e == hipSuccess; ++b) {
+        e = hipMalloc(&t.dev[b], total);
+        if (e == hipSuccess) e = hipHostMalloc(&t.host[b], total, hipHostMallocDefault);
     }
     if (deep) {
         // the stream of the marching class, which runs in the deep one's place or not at
@@ -183,13 +184,26 @@ static int class_of(Server *s, const Model *m, bool deep = false)
         // four hardware queues (500 mixed requests to 2048^2 and 256^3: 7.2 s so, 6.8 s shared)
         k.tiny = 0;
         const auto march = s->class_index.find(k);
-        if (march == s->class_index.end()) return -1;
-        t.stream = s->classes[march->second].stream;
-        t.join = s->classes[march->second].join;
+        if (march == s->class_index.end()) {
+            if (e == hipSuccess) e = hipErrorNotFound;
+        } else {
+            t.stream = s->classes[march->second].stream;
+            t.join = s->classes[march->second].join;
+        }
         k.tiny = 2;
     } else {
-        if (hipStreamCreateWithFlags(&t.stream, hipStreamNonBlocking) != hipSuccess) return -1;
-        if (hipEventCreateWithFlags(&t.join, hipEventDisableTiming) != hipSuccess) return -1;
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&t.stream, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&t.join, hipEventDisableTiming);
+    }
+    if (e != hipSuccess) {
+        // the request goes without this class; a later one tries again
+        (void)hip_fail(e, "class tables");
+        for (int b = 0; b < 2; ++b) {
+            if (t.dev[b]) (void)hipFree(t.dev[b]);
+            if (t.host[b]) (void)hipHostFree(t.host[b]);
+        }
+        if (!deep && t.stream) (void)hipStreamDestroy(t.stream);
+        return -1;
     }
     const int idx = (int)s->classes.size();
     s->classes.push_back(t);
@@ -392,8 +406,12 @@ static void tune_served(Server *s, Req *r)
     int32_t best = keep;
     if (!t.tune_dev) {
         const size_t total = t.args_bytes + sizeof(int32_t) * (2 * s->max_slots + 2);
-        if (hipMalloc(&t.tune_dev, total) != hipSuccess ||
-            hipHostMalloc(&t.tune_host, total, hipHostMallocDefault) != hipSuccess) {
+        hipError_t e = hipMalloc(&t.tune_dev, total);
+        if (e == hipSuccess) e = hipHostMalloc(&t.tune_host, total, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            (void)hip_fail(e, "tuning table");
+            if (t.tune_dev) (void)hipFree(t.tune_dev);
+            t.tune_dev = t.tune_host = nullptr;
             s->tuned[key] = {keep, 0.0};
             return;
         }
